@@ -109,7 +109,8 @@ typedef struct {
     int32_t M0;         /* list cap; 2 <= M0 <= 256 */
     int64_t chunk_rows; /* rows of W_out per Gram block: the library holds
                            chunk_rows x V fp32 scores in device scratch; 0
-                           selects about 2 GiB */
+                           lets the library choose (8 KiB per row up to
+                           4 GiB, or blocks of about 2 GiB) */
 } vie_gpu_build_params;
 
 /* Builds a single-layer graph over the V rows of W_dev (device memory,
@@ -134,8 +135,8 @@ typedef struct {
  * of them should not race with another on the same index).  The index
  * reports M = max(2, M0 / 2)
  * (capped at M0), ef_construction = K, seed 0.  The call allocates device
- * scratch (chunk_rows x V x 4 bytes of scores plus about V (8K + 16 M0)
- * bytes) and releases it before returning; it enqueues on hip_stream and
+ * scratch (chunk_rows x V x 4 bytes of scores, or as chunk_rows = 0 says,
+ * plus about V (8K + 16 M0) bytes and a sample of the rows) and releases it before returning; it enqueues on hip_stream and
  * waits for it.
  * Errors: VIE_EINVAL (NULL, sizes, params), VIE_EUNSUPPORTED (rows not
  * 16-byte aligned), VIE_ENOMEM, VIE_EHIP (a HIP call or launch failed). */

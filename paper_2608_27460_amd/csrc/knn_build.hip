@@ -14,13 +14,18 @@
 //      (score desc, id asc) order, cut at M0 entries;
 //   5. entry point: the row of largest squared norm (ties: smaller id).
 //
-// Step 1 is a dense contraction: the Gram block S = W[rows] W^T of a chunk of
-// rows comes from this file's matrix-core kernel (fp32 accumulation), and
-// one workgroup per row selects its exact top K from S.  Scores are fp32 throughout; ties of equal scores are
+// Step 1 is a dense contraction on the matrix cores (fp32 accumulation).
+// Large heads multiply every pair of rows once and keep only the scores that
+// pass a sampled threshold of either row (knn_pairs_kernel).  Small heads,
+// callers that bound the scores in memory and the rows whose threshold did
+// not serve take the chunked form: the Gram block S = W[rows] W^T of a chunk
+// of rows (knn_gram_kernel), then one workgroup per row selects its exact
+// top K from S (knn_topk_kernel).  Scores are fp32 throughout; ties of equal scores are
 // broken by id exactly as the oracle breaks them.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
 #include <cstring>
 #include <type_traits>
@@ -255,9 +260,10 @@ __device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c)
 }
 
 template <bool BF16>
-__global__ __launch_bounds__(kGramThreads) __attribute__((amdgpu_waves_per_eu(2))) void knn_gram_kernel(const char *__restrict__ W, int64_t V, int row_bytes,
-                                                                int64_t r0, int64_t rows, float *__restrict__ S,
-                                                                int64_t ld)
+__global__ __launch_bounds__(kGramThreads) __attribute__((amdgpu_waves_per_eu(2))) void knn_gram_kernel(const char *__restrict__ W, int row_bytes,
+                                                                const int32_t *__restrict__ list, int64_t r0,
+                                                                int64_t rows, const char *__restrict__ WB, int64_t VB,
+                                                                float *__restrict__ S, int64_t ld)
 {
     extern __shared__ __align__(16) char smem[];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
@@ -273,7 +279,7 @@ __global__ __launch_bounds__(kGramThreads) __attribute__((amdgpu_waves_per_eu(2)
     // workgroups past the last tile return at once.
     const int nc = (int)((rows + kGramTileC - 1) / kGramTileC);
     const int nch = (nc + 1) / 2;
-    const int64_t nj = (V + kGramTile - 1) / kGramTile;
+    const int64_t nj = (VB + kGramTile - 1) / kGramTile;
     const int64_t wg = blockIdx.x, i = wg >> 3, x = wg & 7;
     const int64_t jt = (i / nch) * 4 + (x >> 1), ct = (x & 1) * nch + i % nch;
     if (jt >= nj || ct >= nc) return;
@@ -290,9 +296,9 @@ __global__ __launch_bounds__(kGramThreads) __attribute__((amdgpu_waves_per_eu(2)
         const int L = t * kGramThreads + tid;
         const int srow = L / (kGramKC / 16);  // 0..255: A rows then B rows
         scol[t] = (L % (kGramKC / 16)) * 16;
-        const int64_t grow = srow < kGramTileC ? r0 + min<int64_t>(c0 + srow, rows - 1)
-                                               : min<int64_t>(j0 + srow - kGramTileC, V - 1);
-        src[t] = W + grow * (int64_t)row_bytes;
+        const int64_t arow = r0 + min<int64_t>(c0 + srow, rows - 1);
+        src[t] = srow < kGramTileC ? W + (list ? (int64_t)list[arow] : arow) * row_bytes
+                                   : WB + min<int64_t>(j0 + srow - kGramTileC, VB - 1) * row_bytes;
         soff[t] = gram_piece(srow, scol[t] >> 4);
     }
     auto load_stage = [&](int st, u32x4(&buf)[kGramLoads]) {
@@ -376,17 +382,335 @@ __global__ __launch_bounds__(kGramThreads) __attribute__((amdgpu_waves_per_eu(2)
             float *out = S + c * ld + j0 + wn * 64;
 #pragma unroll
             for (int n = 0; n < 4; ++n)
-                if (j0 + wn * 64 + n * 16 + r < V) out[n * 16 + r] = acc[m][n][i];
+                if (j0 + wn * 64 + n * 16 + r < VB) out[n * 16 + r] = acc[m][n][i];
         }
 }
 
-__global__ __launch_bounds__(kTopkThreads) void knn_topk_kernel(const float *__restrict__ S, int64_t ld, int64_t r0,
+// ---------------------------------------------------------------------------
+// every pair of rows once
+// ---------------------------------------------------------------------------
+//
+// The scores are symmetric, and a row needs only its K best of V.  So each
+// unordered pair of rows is multiplied once, in 256 x 128 tiles of the upper
+// triangle, and no score reaches HBM: a score that reaches the threshold of
+// either of its rows is appended, as a key, to the keys of that row.  A
+// row's threshold is a sampled score (knn_threshold_kernel) with about three
+// times K scores above it; a row whose keys turn out fewer than K or more
+// than kPairCap is left to the chunked form, so the sample decides the speed
+// only, never the result.
+//
+// Bound by the matrix cores.  151936 x 1024 bf16: 25.5 ms for 23.6 TFLOP (0.93
+// PFLOP/s; an 8192-cubed library product reaches 1.21), where the chunked form
+// multiplied every pair twice (63.6 ms), wrote 92 GB of scores and read them
+// back (21.3 ms of selection); with sampling and picking the step takes 33
+// ms instead of 85.  32768 x 256 fp32: 2.7 ms (5.6 chunked) at 100 TFLOP/s.
+//
+// A wave owns a 64 x 64 block of the tile as 4 x 4 tiles of 16 x 16 (the
+// layout, and so every score's sequence of products and sums, is that of
+// knn_gram_kernel).  Stages of 64 bytes of each row go from memory straight
+// to LDS (global_load_lds, 16 bytes a lane), kPairBufs - 1 stages ahead, so
+// no register holds a load in flight and two workgroups fit a CU: one fills
+// the matrix cores while the other waits or sifts its scores.  Piece p of
+// staged row x sits at p ^ ((x >> 2) & 3): the 16 rows of an operand read
+// then hit every LDS bank once.
+
+constexpr int kPairTileC = 256, kPairTileJ = 128;  // rows c and j of a tile
+constexpr int kPairWavesJ = kPairTileJ / 64;
+constexpr int kPairThreads = (kPairTileC / 64) * kPairWavesJ * kWave;
+constexpr int kPairKC = 64;    // bytes of a row per stage
+constexpr int kPairBufs = 3;
+constexpr int kPairRows = kPairTileC + kPairTileJ;
+constexpr int kPairStage = kPairRows * kPairKC;
+constexpr int kPairLoads = kPairStage / (16 * kPairThreads);  // 16-byte loads per lane and stage
+static_assert(kPairLoads * kPairThreads * 16 == kPairStage, "staging shape");
+static_assert(kPairTileC % (kPairThreads / 4) == 0, "one load covers rows c or rows j, never both");
+constexpr int kPairLds = kPairBufs * kPairStage + kPairRows * 4;
+constexpr int kPairList = kPairBufs * kPairStage / 8 / (kPairThreads / kWave);  // listed scores per wave
+constexpr int kPairCap = 1024;        // keys kept per row
+// Heads from this many rows on take this form: per build, against the chunked
+// form, 6000 / 12000 / 20000 / 32768 rows of 256 fp32 values took 3.9 / 5.4 /
+// 7.4 / 11.7 ms (3.5 / 5.2 / 8.2 / 14.8), of 1024 bf16 values 4.2 / 4.7 / 6.1 /
+// 8.9 ms (4.3 / 4.6 / 6.8 / 11.6): below, the sampling costs what it saves.
+constexpr int kPairMinRows = 16384;
+constexpr int kPairPickRows = 4096;   // sampled rows, at least (or V)
+constexpr int kPairPickStep = 32;     // sampled rows, at least one in this many
+
+__device__ __forceinline__ int pair_piece(int x, int p) { return x * kPairKC + ((p ^ ((x >> 2) & 3)) << 4); }
+
+// Appends a key to the keys of a row (more than kPairCap are counted only).
+__device__ __forceinline__ void pair_append(int64_t row, uint64_t key, uint32_t *count, uint64_t *keys)
+{
+    const uint32_t slot = atomicAdd(&count[row], 1u);
+    if (slot < (uint32_t)kPairCap) keys[row * kPairCap + slot] = key;
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void knn_pairs_kernel(
+    const char *__restrict__ W, int64_t V, int row_bytes, int sb, const float *__restrict__ thr, uint32_t *count,
+    uint64_t *keys)
+{
+    extern __shared__ __align__(16) char smem[];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int r = lane & 15, g = lane >> 4;
+    const int wm = wave / kPairWavesJ, wn = wave % kPairWavesJ;
+    // Launch order: blocks of sb x sb squares of kPairTileC rows, walked over
+    // the upper triangle and dealt to the XCDs in turn (workgroup L runs on
+    // XCD L % 8), so that the tiles an XCD works on at a time share their
+    // rows in its L2.  Workgroups past the triangle return at once.
+    constexpr int F = kPairTileC / kPairTileJ;
+    const uint32_t per = (uint32_t)(sb * sb * F), i0 = blockIdx.x >> 3;
+    const uint32_t blk = (i0 / per) * 8 + (blockIdx.x & 7), in = i0 % per;
+    uint32_t bj = (uint32_t)((sqrtf(8.0f * (float)blk + 1.0f) - 1.0f) * 0.5f);
+    while (bj * (bj + 1) / 2 > blk) --bj;
+    while ((bj + 1) * (bj + 2) / 2 <= blk) ++bj;
+    const uint32_t bi = blk - bj * (bj + 1) / 2;
+    const int64_t c0 = (int64_t)(bi * sb + in % sb) * kPairTileC;
+    const int64_t j0 = (int64_t)(bj * sb * F + in / sb) * kPairTileJ;
+    if (c0 >= V || j0 >= V || j0 + kPairTileJ - 1 <= c0) return;
+    float *lthr = reinterpret_cast<float *>(smem + kPairBufs * kPairStage);
+
+    const int nfull = row_bytes / kPairKC;  // whole stages
+    uint32_t off[kPairLoads];               // from the tile's first row c or j
+#pragma unroll
+    for (int t = 0; t < kPairLoads; ++t) {
+        const int x = (t * kPairThreads + tid) / 4;  // staged row
+        const int p = (tid & 3) ^ ((x >> 2) & 3);
+        const int64_t n = x < kPairTileC ? min<int64_t>(x, V - 1 - c0) : min<int64_t>(x - kPairTileC, V - 1 - j0);
+        off[t] = (uint32_t)n * (uint32_t)row_bytes + 16 * p;
+    }
+    const char *baseC = W + c0 * row_bytes, *baseJ = W + j0 * row_bytes;
+    auto issue = [&](int st, int buf) {
+        const int64_t so = (int64_t)min(st, nfull - 1) * kPairKC;  // past the end: the last stage again, unused
+#pragma unroll
+        for (int t = 0; t < kPairLoads; ++t) {
+            const char *base = t * (kPairThreads / 4) < kPairTileC ? baseC : baseJ;
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void *)(base + so + off[t]),
+                (__attribute__((address_space(3))) void *)(smem + buf * kPairStage + (t * kPairThreads + wave * kWave) * 16),
+                16, 0, 0);
+        }
+    };
+    f32x4 acc[4][4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int n = 0; n < 4; ++n) acc[m][n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    auto multiply = [&](const char *buf) {
+        const char *A = buf, *B = buf + kPairTileC * kPairKC;
+        const int ra = wm * 64 + r, rb = wn * 64 + r;
+        if constexpr (BF16) {
+            u32x4 a[4], b[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) a[m] = *reinterpret_cast<const u32x4 *>(A + pair_piece(ra + m * 16, g));
+#pragma unroll
+            for (int n = 0; n < 4; ++n) b[n] = *reinterpret_cast<const u32x4 *>(B + pair_piece(rb + n * 16, g));
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+#pragma unroll
+                for (int n = 0; n < 4; ++n) acc[m][n] = mfma_bf16(a[m], b[n], acc[m][n]);
+        } else {
+#pragma unroll
+            for (int kk = 0; kk < kPairKC / 16; ++kk) {
+                float a[4], b[4];
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+                    a[m] = *reinterpret_cast<const float *>(A + pair_piece(ra + m * 16, kk) + 4 * g);
+#pragma unroll
+                for (int n = 0; n < 4; ++n)
+                    b[n] = *reinterpret_cast<const float *>(B + pair_piece(rb + n * 16, kk) + 4 * g);
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+#pragma unroll
+                    for (int n = 0; n < 4; ++n) acc[m][n] = mfma_f32(a[m], b[n], acc[m][n]);
+                __builtin_amdgcn_sched_barrier(0);  // one step's operands in registers at a time
+            }
+        }
+    };
+    if (nfull > 0) {
+#pragma unroll
+        for (int st = 0; st < kPairBufs - 1; ++st) issue(st, st);
+    }
+    // thresholds of the tile's rows; a row with too many keys takes no more
+    for (int x = tid; x < kPairRows; x += kPairThreads) {
+        const int64_t row = x < kPairTileC ? c0 + x : j0 + x - kPairTileC;
+        float t = __builtin_inff();
+        if (row < V && __hip_atomic_load(&count[row], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <= (uint32_t)kPairCap)
+            t = thr[row];
+        lthr[x] = t;
+    }
+    int slot = 0;  // buffer of stage st
+    for (int st = 0; st < nfull; ++st) {
+        // this wave's loads of stage st have landed (those of the stages
+        // ahead may be in flight) and its reads of stage st - 1 are done;
+        // past the barrier that holds for every wave
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((kPairBufs - 2) * kPairLoads) : "memory");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        issue(st + kPairBufs - 1, slot == 0 ? kPairBufs - 1 : slot - 1);
+        multiply(smem + slot * kPairStage);
+        slot = slot == kPairBufs - 1 ? 0 : slot + 1;
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (row_bytes % kPairKC) {  // the rest of the rows, zeros past it
+#pragma unroll
+        for (int t = 0; t < kPairLoads; ++t) {
+            const int x = (t * kPairThreads + tid) / 4;
+            const int at = nfull * kPairKC + (((tid & 3) ^ ((x >> 2) & 3)) << 4);
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if (at < row_bytes)
+                v = *reinterpret_cast<const u32x4 *>((x < kPairTileC ? baseC : baseJ) + off[t] + nfull * kPairKC);
+            *reinterpret_cast<u32x4 *>(smem + (t * kPairThreads + tid) * 16) = v;
+        }
+        __syncthreads();
+        multiply(smem);
+        __syncthreads();
+    }
+    // Sift: lane (r, g) holds rows c 16 m + 4 g + i of its block, row j
+    // 16 n + r.  Scores that reach a threshold are listed by the wave (its
+    // own part of LDS) and then appended together: the appends of a whole
+    // tile share one round trip.
+    uint64_t *list = reinterpret_cast<uint64_t *>(smem) + wave * kPairList;
+    const float *tcp = lthr + wm * 64 + 4 * g, *tjp = lthr + kPairTileC + wn * 64 + r;
+    float tj[4];
+#pragma unroll
+    for (int n = 0; n < 4; ++n) tj[n] = tjp[16 * n];
+    uint32_t nl = 0;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const f32x4 tc = *reinterpret_cast<const f32x4 *>(tcp + 16 * m);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int n = 0; n < 4; ++n) {
+                const float sc = acc[m][n][i];
+                const bool hc = !(sc < tc[i]), hj = !(sc < tj[n]);
+                if (__ballot(hc || hj) == 0ull) continue;
+                const uint32_t cl = wm * 64 + 16 * m + 4 * g + i, jl = wn * 64 + 16 * n + r;
+                const int64_t c = c0 + cl, j = j0 + jl;
+                const bool hit = (hc || hj) && c < j && j < V;  // c < j: every pair once
+                const uint64_t mask = __ballot(hit);
+                const uint32_t at = nl + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                nl += (uint32_t)__popcll(mask);
+                if (!hit) continue;
+                if (at < (uint32_t)kPairList) {
+                    list[at] = ((uint64_t)__float_as_uint(sc) << 32) | (cl | jl << 8 | (uint32_t)hc << 16 | (uint32_t)hj << 17);
+                } else {  // (equal scores beyond the list: rows that take too many keys stop here)
+                    if (hc && __hip_atomic_load(&count[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <= (uint32_t)kPairCap)
+                        pair_append(c, make_key(sc, (int32_t)j), count, keys);
+                    if (hj && __hip_atomic_load(&count[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <= (uint32_t)kPairCap)
+                        pair_append(j, make_key(sc, (int32_t)c), count, keys);
+                }
+            }
+    }
+    nl = min(nl, (uint32_t)kPairList);
+    for (uint32_t e = lane; e < nl; e += kWave) {
+        const uint64_t v = list[e];
+        const float sc = __uint_as_float((uint32_t)(v >> 32));
+        const int64_t c = c0 + (v & 255), j = j0 + (v >> 8 & 255);
+        if (v & (1u << 16)) pair_append(c, make_key(sc, (int32_t)j), count, keys);
+        if (v & (1u << 17)) pair_append(j, make_key(sc, (int32_t)c), count, keys);
+    }
+}
+
+// Threshold of each row of a chunk from its scores against the sampled rows
+// (sampled row p is row p * step of W_out): the want-th largest, the row
+// itself left out.  A histogram of the scores' top bits finds the bucket it
+// falls in, and the keys from that bucket up are ranked (more than kGatherCap
+// of them: the bucket's lower edge, still a valid threshold).
+__global__ __launch_bounds__(kTopkThreads) void knn_threshold_kernel(const float *__restrict__ S, int64_t ld,
+                                                                     int64_t r0, int64_t np, int step, int want,
+                                                                     float *__restrict__ thr)
+{
+    __shared__ TopkShared sh;
+    const int tid = threadIdx.x;
+    const int64_t i = r0 + blockIdx.x;
+    const float *row = S + (int64_t)blockIdx.x * ld;
+    for (int b = tid; b < kDigitBuckets; b += kTopkThreads) sh.hist[b] = 0u;
+    if (tid == 0) {
+        sh.n = 0u;
+        sh.count = 0u;
+        thr[i] = -__builtin_inff();
+    }
+    __syncthreads();
+    for (int64_t p = tid; p < np; p += kTopkThreads)
+        if (p * step != i) atomicAdd(&sh.hist[f2ord(row[p]) >> (32 - kDigitBits)], 1u);
+    __syncthreads();
+    constexpr int per = kDigitBuckets / kTopkThreads;
+    uint32_t c[per], sum = 0;
+#pragma unroll
+    for (int j = 0; j < per; ++j) {
+        c[j] = sh.hist[kDigitBuckets - 1 - (per * tid + j)];
+        sum += c[j];
+    }
+    uint32_t above = block_exclusive_scan<kTopkThreads>(sum, sh.wsum);
+#pragma unroll
+    for (int j = 0; j < per; ++j) {
+        if (above < (uint32_t)want && (uint32_t)want <= above + c[j]) {
+            sh.bucket = (uint32_t)(kDigitBuckets - 1 - (per * tid + j));
+            sh.count = 1u;
+        }
+        above += c[j];
+    }
+    __syncthreads();
+    if (sh.count == 0u) return;  // fewer sampled scores than wanted: no threshold
+    const uint32_t edge = sh.bucket << (32 - kDigitBits);
+    for (int64_t p = tid; p < np; p += kTopkThreads) {
+        const uint32_t o = f2ord(row[p]);
+        if (o >= edge && p * step != i) {
+            const uint32_t slot = atomicAdd(&sh.n, 1u);
+            if (slot < (uint32_t)kGatherCap) sh.gat[slot] = ((uint64_t)o << 32) | (uint32_t)p;
+        }
+    }
+    __syncthreads();
+    const int m = (int)sh.n;
+    if (m > kGatherCap) {
+        if (tid == 0) thr[i] = ord2f(edge);
+        return;
+    }
+    for (int t = tid; t < m; t += kTopkThreads) {
+        const uint64_t key = sh.gat[t];
+        int rank = 0;
+        for (int u = 0; u < m; ++u) rank += sh.gat[u] > key;
+        if (rank == want - 1) thr[i] = ord2f((uint32_t)(key >> 32));
+    }
+}
+
+// The K best of a row's keys, sorted; a row whose threshold kept fewer than K
+// or more than kPairCap is put on the list of rows left.
+__global__ __launch_bounds__(kTopkThreads) void knn_pick_kernel(int K, const uint32_t *__restrict__ count,
+                                                                const uint64_t *__restrict__ keys,
+                                                                int32_t *__restrict__ cand,
+                                                                float *__restrict__ cand_score,
+                                                                uint32_t *__restrict__ nleft,
+                                                                int32_t *__restrict__ left)
+{
+    __shared__ uint64_t a[kPairCap];
+    const int64_t i = blockIdx.x;
+    const uint32_t n = count[i];
+    if (n < (uint32_t)K || n > (uint32_t)kPairCap) {
+        if (threadIdx.x == 0) left[atomicAdd(nleft, 1u)] = (int32_t)i;
+        return;
+    }
+    for (uint32_t t = threadIdx.x; t < n; t += kTopkThreads) a[t] = keys[i * kPairCap + t];
+    block_sort_desc<kTopkThreads>(a, (int)n);
+    for (int t = threadIdx.x; t < K; t += kTopkThreads) {
+        cand[i * K + t] = key_id(a[t]);
+        cand_score[i * K + t] = key_logit(a[t]);
+    }
+}
+
+__global__ __launch_bounds__(kTopkThreads) void knn_topk_kernel(const float *__restrict__ S, int64_t ld,
+                                                                const int32_t *__restrict__ list, int64_t r0,
                                                                 int64_t V, int K, int32_t *__restrict__ cand,
                                                                 float *__restrict__ cand_score)
 {
     __shared__ TopkShared sh;
     const int tid = threadIdx.x;
-    const int64_t i = r0 + blockIdx.x;
+    const int64_t i = list ? list[r0 + blockIdx.x] : r0 + blockIdx.x;
     const float *row = S + (int64_t)blockIdx.x * ld;
     auto key_at = [&](int64_t j) -> uint64_t { return j == i ? 0ull : make_key(row[j], (int32_t)j); };
 
@@ -807,9 +1131,13 @@ struct Buffers {
     uint64_t *rev = nullptr;
     unsigned long long *best = nullptr;
     char *sample = nullptr;  // the rows of W_out the fingerprint samples, gathered
+    char *pick = nullptr;    // the rows the thresholds are sampled from, gathered
+    float *thr = nullptr;    // threshold of every row
+    uint32_t *nleft = nullptr;
+    int32_t *left = nullptr;  // rows whose threshold did not serve
     void release()
     {
-        void *p[] = {S, cand, fwd, nfwd, cand_score, fwd_score, count, roff, rev, best, sample};
+        void *p[] = {S, cand, fwd, nfwd, cand_score, fwd_score, count, roff, rev, best, sample, pick, thr, nleft, left};
         for (void *q : p)
             if (q) (void)hipFree(q);
         S = nullptr;
@@ -819,7 +1147,10 @@ struct Buffers {
         roff = nullptr;
         rev = nullptr;
         best = nullptr;
-        sample = nullptr;
+        sample = pick = nullptr;
+        thr = nullptr;
+        nleft = nullptr;
+        left = nullptr;
     }
     void release_graph()
     {
@@ -848,10 +1179,16 @@ vie_status build_knn_graph_gpu(const void *W_dev, int dtype, int64_t V, int d, i
                                hipStream_t s, Graph &g, DeviceGraph &dg)
 {
     const int row_bytes = d * elem_bytes(dtype);
+    // Scores of all pairs at once (knn_pairs_kernel) unless the caller bounds
+    // the scores in memory, the keys would pass 4 GiB, or the head is small
+    // enough for the chunked form.
+    const bool pairs = chunk_rows == 0 && V >= kPairMinRows && V * (int64_t)(kPairCap * 8) <= ((int64_t)4 << 30);
     const int64_t ld = (V + 3) & ~(int64_t)3;  // 16-byte aligned rows of scores
     int64_t R = chunk_rows > 0 ? chunk_rows : ((int64_t)2 << 30) / (ld * 4);
+    if (pairs) R = V * (int64_t)(kPairCap * 8) / (ld * 4);  // the rows left over, in the keys' memory
     R = std::max<int64_t>(1, std::min<int64_t>(R, V));
     if (R * ld > ((int64_t)1 << 31)) return fail(VIE_EUNSUPPORTED, "GPU build: a score chunk of %lld rows is too large", (long long)R);
+    const size_t score_bytes = pairs ? (size_t)V * kPairCap * 8 : (size_t)R * ld * 4;
     int dev = 0;
     hipError_t he = hipGetDevice(&dev);
     if (he != hipSuccess) return fail(VIE_EHIP, "hipGetDevice: %s", hipGetErrorString(he));
@@ -865,13 +1202,18 @@ vie_status build_knn_graph_gpu(const void *W_dev, int dtype, int64_t V, int d, i
     // the rows the W_out fingerprint samples: every step-th row, then the last
     const int64_t step = V / 1024 > 1 ? V / 1024 : 1;
     const int64_t nreg = (V + step - 1) / step;
-    if (!dalloc(b.S, (size_t)R * ld * 4) || !dalloc(b.cand, (size_t)V * K * 4) ||
+    // the rows the thresholds are sampled from: every pick_step-th
+    const int pick_step = (int)std::max<int64_t>(1, std::min<int64_t>(kPairPickStep, V / kPairPickRows));
+    const int64_t npick = (V + pick_step - 1) / pick_step;
+    if (!dalloc(b.S, score_bytes) || !dalloc(b.cand, (size_t)V * K * 4) ||
         !dalloc(b.cand_score, (size_t)V * K * 4) || !dalloc(b.fwd, (size_t)edges * 4) ||
         !dalloc(b.fwd_score, (size_t)edges * 4) || !dalloc(b.nfwd, (size_t)V * 4) ||
         !dalloc(b.count, (size_t)V * 4) || !dalloc(b.roff, (size_t)(V + 1) * 8) ||
         !dalloc(b.rev, (size_t)edges * 8) || !dalloc(b.best, 8) || !dalloc(b.adj0, (size_t)edges * 4) ||
         !dalloc(b.upper_off, (size_t)V * 4) || !dalloc(b.upper, 4) ||
-        !dalloc(b.sample, (size_t)(nreg + 1) * row_bytes)) {
+        !dalloc(b.sample, (size_t)(nreg + 1) * row_bytes) ||
+        (pairs && (!dalloc(b.pick, (size_t)npick * row_bytes) || !dalloc(b.thr, (size_t)V * 4) ||
+                   !dalloc(b.nleft, 4) || !dalloc(b.left, (size_t)V * 4)))) {
         b.release();
         b.release_graph();
         return fail(VIE_ENOMEM, "GPU build: device allocation failed (V = %lld, chunk of %lld rows)", (long long)V,
@@ -890,16 +1232,67 @@ vie_status build_knn_graph_gpu(const void *W_dev, int dtype, int64_t V, int d, i
     auto gram = dtype == VIE_BF16 ? knn_gram_kernel<true> : knn_gram_kernel<false>;
     he = hipFuncSetAttribute((const void *)gram, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kGramStage);
     if (he != hipSuccess) return bail(fail(VIE_EHIP, "GPU build: %s", hipGetErrorString(he)));
-    for (int64_t r0 = 0; r0 < V; r0 += R) {
-        const int64_t rows = std::min(R, V - r0);
-        const dim3 grid((unsigned)((((rows + kGramTileC - 1) / kGramTileC + 1) / 2 * 2) * gram_nj4));
-        gram<<<grid, kGramThreads, 2 * kGramStage, s>>>(static_cast<const char *>(W_dev), V, row_bytes, r0, rows, b.S,
-                                                        ld);
-        he = hipGetLastError();
-        if (he != hipSuccess) break;
-        knn_topk_kernel<<<(unsigned)rows, kTopkThreads, 0, s>>>(b.S, ld, r0, V, K, b.cand, b.cand_score);
-        he = hipGetLastError();
-        if (he != hipSuccess) break;
+    // rows [from, from + rows) (of list, or of W_out) against the nb rows of WB
+    auto launch_gram = [&](const int32_t *list, int64_t from, int64_t rows, const char *WB, int64_t nb, int64_t pitch) {
+        const int64_t nj4 = ((nb + kGramTile - 1) / kGramTile + 3) / 4 * 4;  // tiles of j, rounded up to 4
+        const dim3 grid((unsigned)((((rows + kGramTileC - 1) / kGramTileC + 1) / 2 * 2) * nj4));
+        gram<<<grid, kGramThreads, 2 * kGramStage, s>>>(static_cast<const char *>(W_dev), row_bytes, list, from, rows,
+                                                        WB, nb, b.S, pitch);
+        return hipGetLastError();
+    };
+    // the top K of listed rows (list NULL: of every row), chunk by chunk
+    auto chunked = [&](const int32_t *list, int64_t n) {
+        for (int64_t r0 = 0; r0 < n; r0 += R) {
+            const int64_t rows = std::min(R, n - r0);
+            hipError_t e = launch_gram(list, r0, rows, static_cast<const char *>(W_dev), V, ld);
+            if (e != hipSuccess) return e;
+            knn_topk_kernel<<<(unsigned)rows, kTopkThreads, 0, s>>>(b.S, ld, list, r0, V, K, b.cand, b.cand_score);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    };
+    if (pairs) {
+        const char *W = static_cast<const char *>(W_dev);
+        uint64_t *keys = reinterpret_cast<uint64_t *>(b.S);
+        // sampled scores of every row, in the keys' memory
+        he = hipMemcpy2DAsync(b.pick, (size_t)row_bytes, W, (size_t)pick_step * row_bytes, (size_t)row_bytes,
+                              (size_t)npick, hipMemcpyDeviceToDevice, s);
+        const int64_t pld = (npick + 3) & ~(int64_t)3;
+        const int64_t PR = std::min<int64_t>(V, (int64_t)(score_bytes / (pld * 4)));
+        const double mean = (double)K * npick / V;
+        const int want = (int)std::ceil(mean + 3.5 * std::sqrt(mean) + 2.0);
+        for (int64_t r0 = 0; r0 < V && he == hipSuccess; r0 += PR) {
+            const int64_t rows = std::min(PR, V - r0);
+            he = launch_gram(nullptr, r0, rows, b.pick, npick, pld);
+            if (he != hipSuccess) break;
+            knn_threshold_kernel<<<(unsigned)rows, kTopkThreads, 0, s>>>(b.S, pld, r0, npick, pick_step, want, b.thr);
+            he = hipGetLastError();
+        }
+        if (he == hipSuccess) he = hipMemsetAsync(b.count, 0, (size_t)V * 4, s);
+        if (he == hipSuccess) he = hipMemsetAsync(b.nleft, 0, 4, s);
+        if (he == hipSuccess) {
+            const int64_t nt = (V + kPairTileC - 1) / kPairTileC;
+            const int sb = nt >= 64 ? 8 : nt >= 16 ? 4 : 1;
+            const int64_t nsb = (nt + sb - 1) / sb;
+            const int64_t wgs = (nsb * (nsb + 1) / 2 + 7) / 8 * 8 * sb * sb * (kPairTileC / kPairTileJ);
+            auto kern = dtype == VIE_BF16 ? knn_pairs_kernel<true> : knn_pairs_kernel<false>;
+            he = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kPairLds);
+            if (he == hipSuccess) {
+                kern<<<(unsigned)wgs, kPairThreads, kPairLds, s>>>(W, V, row_bytes, sb, b.thr, b.count, keys);
+                he = hipGetLastError();
+            }
+        }
+        uint32_t nleft = 0;
+        if (he == hipSuccess) {
+            knn_pick_kernel<<<(unsigned)V, kTopkThreads, 0, s>>>(K, b.count, keys, b.cand, b.cand_score, b.nleft, b.left);
+            he = hipGetLastError();
+        }
+        if (he == hipSuccess) he = hipMemcpyAsync(&nleft, b.nleft, 4, hipMemcpyDeviceToHost, s);
+        if (he == hipSuccess) he = hipStreamSynchronize(s);
+        if (he == hipSuccess && nleft > 0) he = chunked(b.left, nleft);
+    } else {
+        he = chunked(nullptr, V);
     }
     if (he != hipSuccess) return bail(fail(VIE_EHIP, "GPU build: Gram / top-k launch: %s", hipGetErrorString(he)));
 

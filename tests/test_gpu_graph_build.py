@@ -98,6 +98,45 @@ def test_integer_hub_rows_with_large_reverse_lists(vie):
     assert np.array_equal(ex["adj0"], g.adj0)
 
 
+@pytest.mark.parametrize("V,d,dtype,K,M0,rows", [
+    (16384, 32, synth.BF16, 128, 64, "random"),   # the smallest head of the pair form, whole stages
+    (16385, 24, synth.BF16, 128, 64, "random"),   # 48-byte rows: no whole stage; one row in the last tile
+    (17001, 40, synth.BF16, 64, 32, "integer"),   # a partial last stage; many equal scores
+    (16897, 20, synth.F32, 100, 32, "random"),    # 80-byte fp32 rows
+    (16500, 104, synth.BF16, 1, 8, "random"),     # K = 1
+    (16640, 32, synth.BF16, 32, 16, "copies"),    # a third of the rows equal: more keys than a row keeps
+    (16400, 16, synth.F32, 16, 8, "zeros"),       # every score equal
+    (16400, 64, synth.BF16, 32, 16, "nonfinite"),  # a NaN and an infinity among the scores
+])
+def test_pair_form_equals_the_chunked_form(vie, V, d, dtype, K, M0, rows):
+    # (the chunked form is the one held against the oracle above; chunk_rows
+    # selects it)
+    say("gpu build (pairs)", V, d, dtype, K, M0, rows)
+    if rows == "integer":
+        W = integer_rows(V, d, dtype, V + d)
+    else:
+        Wf = np.random.default_rng(V + d).standard_normal((V, d)).astype(np.float32)
+        if rows == "copies":
+            Wf[::3] = Wf[0]
+        elif rows == "zeros":
+            Wf[:] = 0
+        elif rows == "nonfinite":
+            Wf[777, 3] = np.nan
+            Wf[9001, 5] = np.inf
+        W = Wf if dtype == synth.F32 else vie_bits(Wf)
+    Wd = vie.host_to_torch(W, dtype).cuda()
+    a = vie.Index.build_gpu(Wd, K, M0)
+    b = vie.Index.build_gpu(Wd, K, M0, chunk_rows=V)
+    torch.cuda.synchronize()
+    assert a.info()["entry"] == b.info()["entry"]
+    assert np.array_equal(a.export()["adj0"], b.export()["adj0"])
+
+
+def vie_bits(Wf):
+    # torch's cast keeps NaN and infinity
+    return torch.from_numpy(Wf).bfloat16().view(torch.int16).numpy().view(np.uint16)
+
+
 @pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
 def test_random_rows_match_the_oracle_up_to_near_ties(vie, dtype):
     V, d, K, M0 = 4000, 128, 64, 32
