@@ -4,7 +4,7 @@
 //                        retrieved ids.
 //   dense_stream_kernel, exact head z = W_out h fused with top-k (Section 3;
 //   dense_slab_kernel,   the dense baseline of Section 4.1): slab logits on
-//   dense_mfma_kernel,   the vector ALUs (one to a few queries) or the
+//   dense_tile_kernel,   the vector ALUs (one to a few queries) or the
 //   dense_merge_kernel   matrix cores (batches), then the top k from the
 //                        slabs' candidate lists.
 //   hnsw_kernel          HNSW k-NN search (Sections 2-3; Malkov & Yashunin
@@ -31,6 +31,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <mutex>
+#include <type_traits>
 
 #include "index.hpp"
 #include "keys.hpp"
@@ -362,6 +363,21 @@ __device__ __forceinline__ void topr_merge(const uint64_t (&o)[kTopR], uint64_t 
                 b[i] = x > y ? x : y;
                 b[i + st] = x > y ? y : x;
             }
+}
+
+// Four keys in descending order.
+__device__ __forceinline__ void sort4_desc(uint64_t (&k)[kTopR])
+{
+    auto order = [&](int i, int j) {
+        const uint64_t x = k[i], y = k[j];
+        k[i] = x > y ? x : y;
+        k[j] = x > y ? y : x;
+    };
+    order(0, 1);
+    order(2, 3);
+    order(0, 2);
+    order(1, 3);
+    order(1, 2);
 }
 
 // The kTopR largest over the lanes whose index differs in the bits of
@@ -895,84 +911,59 @@ __global__ __launch_bounds__(kMergeThreads) void dense_merge_kernel(const float 
 }
 
 // ---------------------------------------------------------------------------
-// dense head, batched bf16: skinny GEMM on the matrix cores
+// dense head, batches: skinny GEMM on the matrix cores
 // ---------------------------------------------------------------------------
 //
-// For several queries at once the slab logits come from
-// v_mfma_f32_16x16x32_bf16 (16 rows of W_out times 16 queries per
-// instruction, fp32 accumulation).  Workgroup w owns a slab of rows; each of
-// its four waves takes 32 rows at a time against all the queries of the pass
-// (NQT 16-query tiles) and walks the row width in stages of KC columns.
+// For several queries at once the slab logits come from the matrix cores, 16
+// rows of W_out times 16 queries per instruction: v_mfma_f32_16x16x32_bf16
+// (fp32 accumulation) for bf16 rows, v_mfma_f64_16x16x4_f64 on the widened
+// values for fp32 rows, whose products are exact in fp64 and whose sums are
+// rounded to fp32 once, as on the vector path.
 //
-// The operand layout of the instruction wants 16 different rows per load,
-// which scatters a wave's accesses over 16 rows (64 bytes of each); loaded
-// that way straight into the operand registers, a 128256 x 3072 bf16 W_out
-// streamed at 3.7-4.8 TB/s per call on MI355X (64 to 4 queries), against
-// 5.0-6.1 TB/s staged.  So each wave stages its rows through its own slice of
-// LDS: a stage is read with non-temporal loads that cover whole contiguous
-// row segments (the next one or two stages are loaded while the current one
-// is multiplied), written to LDS and read back in operand layout: lane
-// (r, g) = (lane % 16, lane / 16) takes columns 32 t + 8 g .. + 7 of step t
-// for its row r and the same columns of its query.  The queries' columns of
-// a stage are staged in LDS once for the four waves (read with the row
-// stage, one stage ahead), which keeps the registers for loads in flight.
-// The slab's logits (16-byte stores) and its kTopR largest keys per query go
+// The kernel streams W_out once, so it is bound by HBM as long as enough
+// bytes are in flight on every CU.  One workgroup of eight waves per CU owns
+// a contiguous run of rows and walks it in blocks of RT x 128 rows, each in
+// stages of KC = 256 / RT bytes of every row.  A stage (each wave's own RT x
+// 16 rows, and the same columns of the pass's queries for all waves) goes
+// from memory straight to LDS (global_load_lds, 16 bytes a lane), NBUF - 1
+// stages ahead and across block ends, so 64 to 96 KB of W_out are in flight
+// per CU at any time and no register holds a load.  Piece p (16 bytes) of a
+// staged row sits at a place of that row that depends on the row, so that
+// the operand reads (16 rows, one piece each) hit every LDS bank once.
+// Columns past the row re-read its last piece and are zeroed when read from
+// LDS (last stage only); rows past the block re-read its last row, which
+// stays in L2.
+//
+// The rows are divided evenly over the workgroups in units of four rows, so
+// no CU streams more than another however ragged the vocabulary.  A block's
+// logits (16-byte stores) and, per query and slab, the kTopR largest keys go
 // to the workspace in the layout of the single-query path, and
-// dense_merge_kernel selects the top k.
+// dense_merge_kernel selects the top k.  Ordering a slab's keys takes longer
+// than a stage, so a slab is all of a workgroup's blocks (64 queries of
+// 128256 x 3072 bf16: 162 us per call with a slab a block, 154 with one);
+// the merge's exact fallback serves the few slabs that hold kTopR of the top
+// k, and above k = 128, where they would be many, a workgroup ends up to four.
 //
-// Staged rows are padded by 32 bytes.  A 16-byte LDS read of 64 lanes takes
-// four cycles on gfx950 when no bank is over-used; measured with the LDS
-// counters, the operand read (16 rows, four 16-byte pieces each) takes four
-// cycles when the row pitch is 32 bytes more than a multiple of 64 and eight
-// cycles (half of them bank conflicts) when it is 16 or 48 more, while the
-// stage writes take eight cycles at any of these pitches.
+// Measured per call with the merge (two matrices in turn; before, register-
+// staged slabs for bf16 and passes of eight queries on the vector ALUs for
+// fp32): 128256 x 2048 fp32, 16 queries 830 -> 203 us, 64 queries 3333 -> 578
+// us (four fifths of it at the fp64 matrix rate); 128256 x 3072 fp32, 4
+// queries 354 -> 294 us; 50257 x 1000 bf16, 5 queries 28.5 -> 24.7 us; 151936
+// x 1024 bf16, 8 / 64 queries 65.7 / 89 -> 60.4 / 85 us; 128256 x 3072 bf16,
+// 16 / 32 / 64 queries 133 / 140 / 155 -> 129 / 134 / 150 us.
 
-#ifndef VIE_MFMA_MIN_B
-#define VIE_MFMA_MIN_B 3
-#endif
-#ifndef VIE_MFMA_MAX_WGS
-#define VIE_MFMA_MAX_WGS 1024
-#endif
-// Stage width (columns) and W stages loaded ahead, per pass size (up to
-// 16, 32 or 64 queries); defaults measured on MI355X.
-#ifndef VIE_MFMA_KC1
-#define VIE_MFMA_KC1 256
-#endif
-#ifndef VIE_MFMA_LA1
-#define VIE_MFMA_LA1 1
-#endif
-#ifndef VIE_MFMA_KC2
-#define VIE_MFMA_KC2 128
-#endif
-#ifndef VIE_MFMA_LA2
-#define VIE_MFMA_LA2 2
-#endif
-#ifndef VIE_MFMA_KC4
-#define VIE_MFMA_KC4 128
-#endif
-#ifndef VIE_MFMA_LA4
-#define VIE_MFMA_LA4 1
-#endif
-
-constexpr int kMfmaWaves = 4;
-constexpr int kMfmaThreads = kMfmaWaves * kWave;
-constexpr int kMfmaMaxNB = 64;                    // queries per pass
-constexpr int kMfmaMinB = VIE_MFMA_MIN_B;
-constexpr int kMfmaMaxWgs = VIE_MFMA_MAX_WGS;
-constexpr int kMfmaRowsPerWave = 32;              // two 16-row tiles
-constexpr int kMfmaRowsPerIter = kMfmaWaves * kMfmaRowsPerWave;
-static_assert(kMfmaMaxWgs <= kMergeThreads, "the merge gives every slab maximum a thread");
-
-#ifndef VIE_MFMA_PAD
-#define VIE_MFMA_PAD 32
-#endif
-constexpr int mfma_pitch(int KC) { return KC * 2 + VIE_MFMA_PAD; }  // LDS bytes per staged row (padded)
-constexpr size_t mfma_lds(int NQT, int KC)
-{
-    return (size_t)(kMfmaWaves * kMfmaRowsPerWave + 16 * NQT) * mfma_pitch(KC);
-}
+constexpr int kTileWaves = 8;
+constexpr int kTileThreads = kTileWaves * kWave;
+constexpr int kTileMaxNB = 64;              // queries per pass
+constexpr int kTileMinB = 3;
+constexpr int kTileWgs = 256;               // one per CU
+constexpr int tile_rows(int RT) { return kTileWaves * 16 * RT; }        // most rows of a block
+constexpr int tile_kc(int RT) { return 256 / RT; }                      // bytes of a row per stage
+constexpr int tile_stage(int NQT, int RT) { return (tile_rows(RT) + 16 * NQT) * tile_kc(RT); }
+constexpr int tile_bufs(int NQT) { return NQT == 1 ? 4 : 3; }            // within 160 KB of LDS
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c)
 {
@@ -980,186 +971,275 @@ __device__ __forceinline__ f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c)
                                                    c, 0, 0, 0);
 }
 
-template <int NQT, int KC, int LA>
-__global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(2))) void dense_mfma_kernel(const uint16_t *__restrict__ W, int64_t V, int d,
-                                                                   const uint16_t *__restrict__ hq, int nq,
-                                                                   int rows_per_wg, float *__restrict__ zout,
-                                                                   uint64_t *__restrict__ tops)
+// 16 bytes per lane from src (per lane) to dst + 16 * lane (dst uniform over the wave)
+template <int AUX> __device__ __forceinline__ void load_lds16(const char *src, char *dst)
 {
-    extern __shared__ __align__(16) char smem[];
-    __shared__ uint64_t s_top[16 * NQT][kMfmaWaves][kTopR];
-    constexpr int kPitch = mfma_pitch(KC);
-    constexpr int kSteps = KC / 32;                     // MFMA steps per stage
-    constexpr int kLanesPerRow = KC / 8;                // 16-byte pieces per staged row
-    constexpr int kRowsPerLoad = kWave / kLanesPerRow;
-    constexpr int kLoads = kMfmaRowsPerWave / kRowsPerLoad;  // W stage loads per lane
-    constexpr int kHLoads = 16 * NQT * kLanesPerRow / kMfmaThreads;  // query stage loads per thread
-    static_assert(kRowsPerLoad >= 1 && kMfmaRowsPerWave % kRowsPerLoad == 0, "stage shape");
-    static_assert(kHLoads >= 1 && (16 * NQT * kLanesPerRow) % kMfmaThreads == 0, "query stage shape");
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int r = lane & 15, g = lane >> 4;
-    char *slice = smem + (size_t)wave * kMfmaRowsPerWave * kPitch;
-    char *hsl = smem + (size_t)kMfmaWaves * kMfmaRowsPerWave * kPitch;  // [16 NQT][kPitch]
-    const int64_t r0 = (int64_t)blockIdx.x * rows_per_wg;
-    const int nrows = (int)max<int64_t>(0, min<int64_t>(rows_per_wg, V - r0));
-    const int nstage = (d + KC - 1) / KC;
-    const u32x4 zero = {0u, 0u, 0u, 0u};
-    // slab starts are multiples of 128 rows, so with V % 4 == 0 every group
-    // of four rows of a query's logits is 16-byte aligned
-    const bool zvec = (V & 3) == 0 && ((uintptr_t)zout & 15) == 0;
-    // W staging: load j of a lane covers row kRowsPerLoad j + srow, 16 bytes
-    // at column scol of the stage
-    const int srow = lane / kLanesPerRow, scol = 8 * (lane % kLanesPerRow);
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                     (__attribute__((address_space(3))) void *)dst, 16, 0, AUX);
+}
 
-    // query staging: load j of a thread covers query row L / kLanesPerRow
-    // (padding rows repeat the last query), column hcol[j]
-    const uint16_t *hrowp[kHLoads];
-    int hoff[kHLoads], hcol[kHLoads];
+// where piece 0 of staged row x sits (piece p at p ^ this)
+template <int KC> __device__ __forceinline__ int tile_swizzle(int x) { return KC == 256 ? x & 15 : x >> 1 & 7; }
+
+template <bool BF16, int NQT, int RT, int AUX>
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void dense_tile_kernel(
+    const char *__restrict__ W, int64_t V, int row_bytes, const char *__restrict__ hq, int nq, int rows_per_blk,
+    int blks_per_slab, int blks_per_wg, int nslab, float *__restrict__ zout, uint64_t *__restrict__ tops)
+{
+    typedef typename std::conditional<BF16, f32x4, f64x4>::type Acc;
+    extern __shared__ __align__(16) char smem[];
+    __shared__ uint64_t s_top[NQT > 1 ? 32 : 16][kTileWaves][kTopR];
+    constexpr int NBUF = tile_bufs(NQT), kStage = tile_stage(NQT, RT), kRows = tile_rows(RT);
+    constexpr int KC = tile_kc(RT), kPieces = KC / 16, kLoadRows = kWave / kPieces;
+    constexpr int kWLoads = 16 * RT / kLoadRows;       // loads of a wave's rows
+    constexpr int kHRows = 16 * NQT / kTileWaves;      // query rows a wave stages
+    constexpr int kHLoads = (kHRows + kLoadRows - 1) / kLoadRows;
+    constexpr int kLoads = kWLoads + kHLoads;          // loads per wave and stage
+    constexpr bool kThrough = 16 * NQT * (kRows + 4) * 4 <= kStage;      // logits leave through LDS
+    constexpr int kZStores = 16 * NQT * (kRows / 4) / kTileThreads;      // 16-byte stores per wave and block
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int r = lane & 15, g = lane >> 4;
+    const int64_t r0 = (int64_t)blockIdx.x * blks_per_wg * rows_per_blk;
+    const int nrows = (int)min<int64_t>((int64_t)blks_per_wg * rows_per_blk, V - r0);
+    const int nblk = (nrows + rows_per_blk - 1) / rows_per_blk;
+    const int nstage = (row_bytes + KC - 1) / KC;
+    const bool ragged = row_bytes % KC != 0;
+    const bool zvec = (V & 3) == 0 && ((uintptr_t)zout & 15) == 0;
+
+    // Staging.  A load covers four staged rows; lane l fills slot l % 16 of
+    // row l / 16 with the piece that belongs there.  Matrix row x of a wave
+    // is its row x, or for fp32 rows row 4 (x % 4) + x / 4: a lane's four
+    // results are four consecutive rows then (in fp64 they lie four apart).
+    const char *wsrc[kWLoads], *hsrc[kHLoads];
+    int wcol[kWLoads], hcol[kHLoads];
+    const int lrow = lane / kPieces, slot = lane % kPieces;
 #pragma unroll
-    for (int j = 0; j < kHLoads; ++j) {
-        const int L = j * kMfmaThreads + tid;
-        const int row = L / kLanesPerRow;
-        hcol[j] = 8 * (L % kLanesPerRow);
-        hrowp[j] = hq + (int64_t)min(row, nq - 1) * d;
-        hoff[j] = row * kPitch + hcol[j] * 2;
+    for (int t = 0; t < kWLoads; ++t) wcol[t] = 16 * (slot ^ tile_swizzle<KC>((kLoadRows * t + lrow) & 15));
+#pragma unroll
+    for (int t = 0; t < kHLoads; ++t) {
+        const int x = wave * kHRows + kLoadRows * t + lrow;
+        hsrc[t] = hq + (int64_t)min(x, nq - 1) * row_bytes;
+        hcol[t] = 16 * (slot ^ tile_swizzle<KC>(x & 15));
     }
+    auto set_block = [&](int b) {
+        const int last = min(rows_per_blk, nrows - b * rows_per_blk) - 1;
+#pragma unroll
+        for (int t = 0; t < kWLoads; ++t) {
+            const int x = kLoadRows * t + lrow;
+            const int row = wave * 16 * RT + (BF16 ? x : (x & ~15) + 4 * (x % 4) + x % 16 / 4);
+            wsrc[t] = W + (r0 + (int64_t)b * rows_per_blk + min(row, last)) * row_bytes;
+        }
+    };
+    auto issue = [&](int st, int buf) {
+        char *dst = smem + buf * kStage;
+        const int c0 = st * KC;
+#pragma unroll
+        for (int t = 0; t < kWLoads; ++t)
+            load_lds16<AUX>(wsrc[t] + min(c0 + wcol[t], row_bytes - 16), dst + (wave * 16 * RT + kLoadRows * t) * KC);
+#pragma unroll
+        for (int t = 0; t < kHLoads; ++t)
+            if (kHRows >= kLoadRows || lane < kHRows * kPieces)
+                load_lds16<0>(hsrc[t] + min(c0 + hcol[t], row_bytes - 16),
+                              dst + (kRows + wave * kHRows + kLoadRows * t) * KC);
+    };
+
+    Acc acc[RT][NQT];
+    auto multiply = [&](const char *buf, int left, auto masked) {
+        const char *A = buf + (wave * 16 * RT + r) * KC, *B = buf + (kRows + r) * KC;
+#pragma unroll
+        for (int t = 0; t < KC / 64; ++t) {
+            const int at = (4 * t + g) ^ tile_swizzle<KC>(r);
+            const bool in = !decltype(masked)::value || 64 * t + 16 * g < left;
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+            u32x4 a[RT], b[NQT];
+#pragma unroll
+            for (int m = 0; m < RT; ++m) {
+                a[m] = *reinterpret_cast<const u32x4 *>(A + m * 16 * KC + 16 * at);
+                a[m] = in ? a[m] : zero;
+            }
+#pragma unroll
+            for (int n = 0; n < NQT; ++n) {
+                b[n] = *reinterpret_cast<const u32x4 *>(B + n * 16 * KC + 16 * at);
+                b[n] = in ? b[n] : zero;
+            }
+            if constexpr (BF16) {
+#pragma unroll
+                for (int m = 0; m < RT; ++m)
+#pragma unroll
+                    for (int n = 0; n < NQT; ++n) acc[m][n] = mfma_bf16(a[m], b[n], acc[m][n]);
+            } else {
+                // (a lane's four values are one column of each of four
+                // steps, the same columns of rows and queries)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    double av[RT];
+#pragma unroll
+                    for (int m = 0; m < RT; ++m) av[m] = (double)__uint_as_float(a[m][e]);
+#pragma unroll
+                    for (int n = 0; n < NQT; ++n) {
+                        const double bv = (double)__uint_as_float(b[n][e]);
+#pragma unroll
+                        for (int m = 0; m < RT; ++m)
+                            acc[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[m], bv, acc[m][n], 0, 0, 0);
+                    }
+                }
+            }
+        }
+    };
 
     uint64_t best[NQT][kTopR];
 #pragma unroll
-    for (int n = 0; n < NQT; ++n)
+    for (int n = 0; n < NQT; ++n) {
+#pragma unroll
+        for (int m = 0; m < RT; ++m) acc[m][n] = Acc{0, 0, 0, 0};
 #pragma unroll
         for (int i = 0; i < kTopR; ++i) best[n][i] = 0ull;
+    }
 
-    // Every wave runs the same number of iterations (the workgroup barriers
-    // need it); rows past the slab are clamped and discarded.  W stages run
-    // LA ahead: stage st's loads sit in buffer st % LA (the loop is unrolled
-    // over the buffers, so no in-flight load is ever copied); the query stage
-    // runs one ahead.  Every stage issues the same loads with no branch
-    // around them, in the order they are consumed (columns past the row are
-    // clamped to its last piece and replaced by zeros when staged; the loads
-    // of stages past the end re-read a query piece, which stays in L2), with
-    // scheduling barriers keeping that order: the compiler then counts the
-    // loads in flight exactly and waits only for the stage being staged, not
-    // for the ones still ahead.
-    for (int rb0 = 0; rb0 < nrows; rb0 += kMfmaRowsPerIter) {
-        const int rb = rb0 + wave * kMfmaRowsPerWave;
-        const uint16_t *wrow[kLoads];
-#pragma unroll
-        for (int j = 0; j < kLoads; ++j)
-            wrow[j] = W + (r0 + min(rb + kRowsPerLoad * j + srow, nrows - 1)) * (int64_t)d;
-        u32x4 pre[LA][kLoads];
-        u32x4 hpre[kHLoads];
-#pragma unroll
-        for (int b = 0; b < LA; ++b) {
-#pragma unroll
-            for (int j = 0; j < kLoads; ++j)
-                pre[b][j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(
-                    b < nstage ? wrow[j] + min(b * KC + scol, d - 8) : hrowp[0]));
-            __builtin_amdgcn_sched_barrier(0);  // keep the issue order
-            if (b == 0) {
-#pragma unroll
-                for (int j = 0; j < kHLoads; ++j)
-                    hpre[j] = *reinterpret_cast<const u32x4 *>(hrowp[j] + min(hcol[j], d - 8));
-                __builtin_amdgcn_sched_barrier(0);
-            }
+    // stages in flight: the next to load is stage lst of block lb
+    int lb = 0, lst = 0;
+    auto load_next = [&](int buf) {
+        issue(lst, buf);
+        if (++lst == nstage) {  // past the last block: its stages again, unused
+            lst = 0;
+            lb = min(lb + 1, nblk - 1);
+            set_block(lb);
         }
-        f32x4 acc[2][NQT];
+    };
+    set_block(0);
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
+    for (int b = 0; b < NBUF - 1; ++b) load_next(b);
+    int buf = 0, stored = 0;
+    for (int b = 0; b < nblk; ++b) {
+        for (int st = 0; st < nstage; ++st) {
+            // this wave's loads of the stage have landed (those of the stages
+            // ahead may be in flight) and its reads of the stage before are
+            // done; past the barrier that holds for every wave.  The first
+            // NBUF - 1 stages after a block's end were issued before its
+            // stores, which may still be in flight too.
+            __builtin_amdgcn_sched_barrier(0);
+            if (stored > 0) {
+                --stored;
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NBUF - 2) * kLoads + kZStores) : "memory");
+            } else {
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NBUF - 2) * kLoads) : "memory");
+            }
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            load_next(buf == 0 ? NBUF - 1 : buf - 1);
+            if (ragged && st == nstage - 1)
+                multiply(smem + buf * kStage, row_bytes - st * KC, std::true_type());
+            else
+                multiply(smem + buf * kStage, 0, std::false_type());
+            buf = buf == NBUF - 1 ? 0 : buf + 1;
+        }
+        // lane (r, g) holds rows 4 g + i of each row tile for query 16 n + r
+        const int live = min(rows_per_blk, nrows - b * rows_per_blk);  // rows of this block
+        f32x4 z[RT][NQT];
 #pragma unroll
-            for (int n = 0; n < NQT; ++n) acc[m][n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-
-        for (int st0 = 0; st0 < nstage; st0 += LA) {
+        for (int m = 0; m < RT; ++m)
 #pragma unroll
-            for (int b = 0; b < LA; ++b) {
-                const int st = st0 + b;
-                if (st >= nstage) break;  // uniform across the workgroup
-                const int c0 = st * KC;
-                __syncthreads();  // every wave is done with the previous query stage
-                // this stage into LDS, then the loads of stage st + 1 (queries)
-                // and st + LA (W)
-                const bool win = c0 + scol + 8 <= d;
+            for (int n = 0; n < NQT; ++n) {
 #pragma unroll
-                for (int j = 0; j < kLoads; ++j)
-                    *reinterpret_cast<u32x4 *>(slice + (kRowsPerLoad * j + srow) * kPitch + scol * 2) =
-                        win ? pre[b][j] : zero;
+                for (int i = 0; i < 4; ++i) z[m][n][i] = (float)acc[m][n][i];
+                acc[m][n] = Acc{0, 0, 0, 0};
+            }
+        // The logits leave through the stage just multiplied (free until the
+        // next stage's barrier): each query's rows of the block as one run.
+        // (Stored from the result layout, 64 bytes a query, they took 24 of
+        // the 93 us of 64 queries over 151936 x 1024 bf16; so, 85 us.)
+        constexpr int kZPitch = kRows + 4;  // floats
+        static_assert(kThrough == (16 * NQT * kZPitch * 4 <= kStage), "logits of a block in a stage");
+        float *zo = zout + r0 + (int64_t)b * rows_per_blk;
+        if constexpr (kThrough) {
+            float *zl = reinterpret_cast<float *>(smem + (buf == 0 ? NBUF - 1 : buf - 1) * kStage);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
 #pragma unroll
-                for (int j = 0; j < kHLoads; ++j)
-                    *reinterpret_cast<u32x4 *>(hsl + hoff[j]) = c0 + hcol[j] + 8 <= d ? hpre[j] : zero;
+            for (int m = 0; m < RT; ++m)
 #pragma unroll
-                for (int j = 0; j < kHLoads; ++j)
-                    hpre[j] = *reinterpret_cast<const u32x4 *>(hrowp[j] + min(c0 + KC + hcol[j], d - 8));
-                __builtin_amdgcn_sched_barrier(0);
-                const bool ahead = st + LA < nstage;
+                for (int n = 0; n < NQT; ++n)
+                    *reinterpret_cast<f32x4 *>(zl + (n * 16 + r) * kZPitch + (wave * RT + m) * 16 + 4 * g) = z[m][n];
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            if (zvec) {  // (the block starts at a multiple of four rows and live is one too)
 #pragma unroll
-                for (int j = 0; j < kLoads; ++j)
-                    pre[b][j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(
-                        ahead ? wrow[j] + min(c0 + LA * KC + scol, d - 8) : hrowp[0]));
-                __syncthreads();  // the query stage is complete
-#pragma unroll
-                for (int t = 0; t < kSteps; ++t) {
-                    u32x4 a[2];
-#pragma unroll
-                    for (int m = 0; m < 2; ++m)
-                        a[m] = *reinterpret_cast<const u32x4 *>(slice + (m * 16 + r) * kPitch + (32 * t + 8 * g) * 2);
-#pragma unroll
-                    for (int n = 0; n < NQT; ++n) {
-                        const u32x4 bv =
-                            *reinterpret_cast<const u32x4 *>(hsl + (n * 16 + r) * kPitch + (32 * t + 8 * g) * 2);
-#pragma unroll
-                        for (int m = 0; m < 2; ++m) acc[m][n] = mfma_bf16(a[m], bv, acc[m][n]);
+                for (int i = 0; i < kZStores; ++i) {
+                    const int q = (i * kTileThreads + tid) / (kRows / 4), c = 4 * (tid % (kRows / 4));
+                    if (q < nq && c < live) {
+                        const f32x4 v = *reinterpret_cast<const f32x4 *>(zl + q * kZPitch + c);
+                        __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(zo + (int64_t)q * V + c));
                     }
                 }
-                __builtin_amdgcn_wave_barrier();
+                // (this wave's last store had a live query, so it made kZStores)
+                if ((kZStores - 1) * (kTileThreads / (kRows / 4)) + wave * kWave / (kRows / 4) < nq) stored = NBUF - 1;
+            } else {
+                for (int i = tid; i < nq * kRows; i += kTileThreads)
+                    if (i % kRows < live) zo[(int64_t)(i / kRows) * V + i % kRows] = zl[i / kRows * kZPitch + i % kRows];
             }
         }
-        // lane (r, g) holds rows 4 g + i of each 16-row tile for query 16 n + r:
-        // one 16-byte store where the four rows exist and are 16-byte aligned
-        // (non-temporal from 32 queries on; measured: a 16-query pass is
-        // faster with ordinary stores, a 32-query pass with non-temporal ones)
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
+        for (int m = 0; m < RT; ++m) {
+            const int lr = (wave * RT + m) * 16 + 4 * g, left = live - lr;
 #pragma unroll
             for (int n = 0; n < NQT; ++n) {
                 const int q = n * 16 + r;
-                const int lr = rb + m * 16 + 4 * g;
-                if (q < nq) {
-                    float *zp = zout + (int64_t)q * V + r0 + lr;
-                    if (zvec && lr + 3 < nrows) {
-                        if constexpr (NQT == 1)
-                            *reinterpret_cast<f32x4 *>(zp) = acc[m][n];
-                        else
-                            __builtin_nontemporal_store(acc[m][n], reinterpret_cast<f32x4 *>(zp));
+                if (q >= nq || left <= 0) continue;
+                if constexpr (!kThrough) {
+                    if (zvec) {
+                        __builtin_nontemporal_store(z[m][n], reinterpret_cast<f32x4 *>(zo + (int64_t)q * V + lr));
                     } else
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
-                            if (lr + i < nrows) zp[i] = acc[m][n][i];
+                            if (i < left) zo[(int64_t)q * V + lr + i] = z[m][n][i];
+                }
+                uint64_t key[kTopR];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (lr + i < nrows) topr_insert(make_key(acc[m][n][i], (int32_t)(r0 + lr + i)), best[n]);
+                for (int i = 0; i < kTopR; ++i)
+                    key[i] = i < left ? make_key(z[m][n][i], (int32_t)(r0 + b * rows_per_blk + lr + i)) : 0ull;
+                sort4_desc(key);
+                if (m == 0 && b % blks_per_slab == 0) {
+#pragma unroll
+                    for (int i = 0; i < kTopR; ++i) best[n][i] = key[i];
+                } else {
+                    topr_merge(key, best[n]);
                 }
             }
-    }
-    // per query: the kTopR largest over the four lane groups, then over the waves
-#pragma unroll
-    for (int n = 0; n < NQT; ++n) {
-        topr_reduce<32, 16>(best[n]);
-        if (g == 0)
-#pragma unroll
-            for (int i = 0; i < kTopR; ++i) s_top[n * 16 + r][wave][i] = best[n][i];
-    }
-    __syncthreads();
-    if (tid < nq) {
-        uint64_t b[kTopR], o[kTopR];
-#pragma unroll
-        for (int i = 0; i < kTopR; ++i) b[i] = s_top[tid][0][i];
-        for (int w = 1; w < kMfmaWaves; ++w) {
-#pragma unroll
-            for (int i = 0; i < kTopR; ++i) o[i] = s_top[tid][w][i];
-            topr_merge(o, b);
         }
-        store_topr(tops + ((int64_t)tid * gridDim.x + blockIdx.x) * kTopR, b);
+        if ((b + 1) % blks_per_slab != 0 && b != nblk - 1) continue;
+        // end of a slab: per query the kTopR largest over the four lane
+        // groups of each wave, then over the waves, one list a lane (32
+        // queries at a time; barriers that leave the loads in flight)
+        const int slab = blockIdx.x * (blks_per_wg / blks_per_slab) + b / blks_per_slab;
+#pragma unroll
+        for (int n0 = 0; n0 < NQT; n0 += 2) {
+#pragma unroll
+            for (int n = n0; n < min(n0 + 2, NQT); ++n) {
+                topr_reduce<32, 16>(best[n]);
+                if (g == 0)
+#pragma unroll
+                    for (int i = 0; i < kTopR; ++i) s_top[(n - n0) * 16 + r][wave][i] = best[n][i];
+#pragma unroll
+                for (int i = 0; i < kTopR; ++i) best[n][i] = 0ull;
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            constexpr int kPer = (NQT > 1 ? 32 : 16) / kTileWaves;  // queries of a wave
+            const int q = wave * kPer + lane / kTileWaves;
+            if (lane < kPer * kTileWaves) {
+                uint64_t t[kTopR];
+#pragma unroll
+                for (int i = 0; i < kTopR; ++i) t[i] = s_top[q][lane % kTileWaves][i];
+                topr_reduce<4>(t);
+                if (lane % kTileWaves == 0 && n0 * 16 + q < nq)
+                    store_topr(tops + ((int64_t)(n0 * 16 + q) * nslab + slab) * kTopR, t);
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+        }
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load into LDS outlives the workgroup
 }
 
 // ---------------------------------------------------------------------------
@@ -2840,43 +2920,86 @@ hipError_t dense_launch_nb(int nb, const void *W, int64_t V, int row_bytes, cons
 
 namespace {
 
-// Matrix-core plan: slabs of whole workgroup iterations, at most
-// kDenseMaxWgs of them (the merge gives every slab maximum a thread).
-DensePlan mfma_plan(int64_t V)
+// Matrix-core plan: blocks of equal rows (a multiple of four, at most
+// tile_rows), the same number for each of at most kTileWgs workgroups, and
+// slabs of as many blocks as keep them within one thread each of the merge.
+struct TilePlan {
+    int row_tiles, rows_per_blk, blks_per_slab, blks_per_wg, nwg, nslab;
+};
+
+// Two row tiles a wave where a workgroup has the rows (128 or fewer would
+// leave half of it without), except for many bf16 queries: measured with two
+// against one, 128256 x 3072 bf16 134 against 137 us (16 queries) but 139
+// against 134 (32) and 161 against 154 (64); 128256 x 2048 fp32 207 against
+// 219 us (16) and 582 against 609 (64).  A slab: see above (k).
+TilePlan tile_plan(int64_t V, bool bf16, int nq, int k)
 {
-    const int64_t iters = (V + kMfmaRowsPerIter - 1) / kMfmaRowsPerIter;
-    const int64_t per = (iters + kMfmaMaxWgs - 1) / kMfmaMaxWgs;
-    DensePlan p;
-    p.rpw = (int)(per * kMfmaRowsPerIter);
-    p.nwg = (int)((V + p.rpw - 1) / p.rpw);
-    p.nbmax = kMfmaMaxNB;
+    TilePlan p;
+    p.row_tiles = V > (int64_t)tile_rows(1) * kTileWgs && (!bf16 || nq <= 16) ? 2 : 1;
+    const int64_t round = (int64_t)tile_rows(p.row_tiles) * kTileWgs;
+    int64_t per = (V + round - 1) / round;
+    const int slabs = k <= 128 ? 1 : kMergeThreads / kTileWgs;  // slabs of a workgroup, at most
+    p.blks_per_slab = (int)((per + slabs - 1) / slabs);
+    per = (per + p.blks_per_slab - 1) / p.blks_per_slab * p.blks_per_slab;
+    p.blks_per_wg = (int)per;
+    p.rows_per_blk = (int)(((V + per * kTileWgs - 1) / (per * kTileWgs) + 3) / 4 * 4);
+    const int64_t slab_rows = (int64_t)p.rows_per_blk * p.blks_per_slab;
+    p.nwg = (int)((V + p.rows_per_blk * per - 1) / (p.rows_per_blk * per));
+    p.nslab = (int)((V + slab_rows - 1) / slab_rows);
     return p;
 }
 
-bool use_mfma(int dtype, int d, int B, const void *W, const void *h)
+bool use_tiles(int row_bytes, int B, const void *W, const void *h)
 {
-    return dtype == VIE_BF16 && B >= kMfmaMinB && d % 8 == 0 && (uintptr_t)W % 16 == 0 && (uintptr_t)h % 16 == 0;
+    return B >= kTileMinB && row_bytes % 16 == 0 && (uintptr_t)W % 16 == 0 && (uintptr_t)h % 16 == 0;
 }
 
 // Queries per pass of either path.
-int dense_pass(int B) { return B >= kMfmaMinB ? kMfmaMaxNB : kDenseMaxNB; }
+int dense_pass(int B) { return B >= kTileMinB ? kTileMaxNB : kDenseMaxNB; }
 
-template <int NQT, int KC, int LA>
-hipError_t mfma_launch(const void *W, int64_t V, int d, const char *h, int nq, int k, const DensePlan &p,
+template <bool BF16, int NQT, int RT, int AUX>
+hipError_t tile_launch(const void *W, int64_t V, int row_bytes, const char *h, int nq, int k, const TilePlan &p,
                        float *zbuf, uint64_t *tops, int32_t *ids, float *logits, hipStream_t s)
 {
-    auto kern = dense_mfma_kernel<NQT, KC, LA>;
-    constexpr size_t lds = mfma_lds(NQT, KC);
-    if (lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
-    kern<<<p.nwg, kMfmaThreads, lds, s>>>(static_cast<const uint16_t *>(W), V, d,
-                                           reinterpret_cast<const uint16_t *>(h), nq, p.rpw, zbuf, tops);
-    hipError_t e = hipGetLastError();
+    auto kern = dense_tile_kernel<BF16, NQT, RT, AUX>;
+    constexpr int lds = tile_bufs(NQT) * tile_stage(NQT, RT);
+    hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
-    dense_merge_kernel<<<nq, kMergeThreads, 0, s>>>(zbuf, tops, V, p.rpw, p.nwg, k, ids, logits);
+    kern<<<p.nwg, kTileThreads, lds, s>>>(static_cast<const char *>(W), V, row_bytes, h, nq, p.rows_per_blk,
+                                          p.blks_per_slab, p.blks_per_wg, p.nslab, zbuf, tops);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    dense_merge_kernel<<<nq, kMergeThreads, 0, s>>>(zbuf, tops, V, p.rows_per_blk * p.blks_per_slab, p.nslab, k, ids,
+                                                    logits);
     return hipGetLastError();
+}
+
+template <bool BF16, int NQT>
+hipError_t tile_launch_form(const void *W, int64_t V, int row_bytes, const char *h, int nq, int k, const TilePlan &p,
+                            float *zbuf, uint64_t *tops, int32_t *ids, float *logits, hipStream_t s)
+{
+    // A W_out that outgrows the 256 MB Infinity Cache is streamed past it
+    // (128256 x 3072 bf16, 64 queries: 154 us per call, 161 without), a
+    // smaller one may still be there at the next call (50257 x 1000 bf16, 5
+    // queries: 25 us, 29 when streamed).
+    constexpr int kNt = 2;
+    const bool nt = V * row_bytes > ((int64_t)256 << 20);
+    // (many bf16 queries run one row tile only)
+    if constexpr (!BF16 || NQT == 1)
+        if (p.row_tiles == 2)
+            return nt ? tile_launch<BF16, NQT, 2, kNt>(W, V, row_bytes, h, nq, k, p, zbuf, tops, ids, logits, s)
+                      : tile_launch<BF16, NQT, 2, 0>(W, V, row_bytes, h, nq, k, p, zbuf, tops, ids, logits, s);
+    return nt ? tile_launch<BF16, NQT, 1, kNt>(W, V, row_bytes, h, nq, k, p, zbuf, tops, ids, logits, s)
+              : tile_launch<BF16, NQT, 1, 0>(W, V, row_bytes, h, nq, k, p, zbuf, tops, ids, logits, s);
+}
+
+template <bool BF16>
+hipError_t tile_launch_nq(const void *W, int64_t V, int row_bytes, const char *h, int nq, int k, const TilePlan &p,
+                          float *zbuf, uint64_t *tops, int32_t *ids, float *logits, hipStream_t s)
+{
+    if (nq <= 16) return tile_launch_form<BF16, 1>(W, V, row_bytes, h, nq, k, p, zbuf, tops, ids, logits, s);
+    if (nq <= 32) return tile_launch_form<BF16, 2>(W, V, row_bytes, h, nq, k, p, zbuf, tops, ids, logits, s);
+    return tile_launch_form<BF16, 4>(W, V, row_bytes, h, nq, k, p, zbuf, tops, ids, logits, s);
 }
 
 }  // namespace
@@ -2891,7 +3014,7 @@ size_t dense_workspace_bytes(int64_t V, int d, int B, int k)
     (void)k;
     const int pass = dense_pass(B);
     const int nb = B < pass ? B : pass;
-    const int slabs = std::max(dense_grid(V), mfma_plan(V).nwg);
+    const int slabs = dense_grid(V);  // tile_plan has no more
     return (((size_t)nb * V * 4 + 255) & ~(size_t)255) + (size_t)nb * slabs * 8 * kTopR;
 }
 
@@ -2909,17 +3032,16 @@ vie_status launch_dense_topk(const void *W, int dtype, int64_t V, int d, const v
     uint64_t *tops = reinterpret_cast<uint64_t *>(static_cast<char *>(ws) +
                                                    (((size_t)nbw * V * 4 + 255) & ~(size_t)255));
     const char *hb = static_cast<const char *>(h);
-    if (use_mfma(dtype, d, B, W, h)) {
-        const DensePlan mp = mfma_plan(V);
-        for (int q0 = 0; q0 < B; q0 += kMfmaMaxNB) {
-            const int nq = B - q0 < kMfmaMaxNB ? B - q0 : kMfmaMaxNB;
+    if (use_tiles(row_bytes, B, W, h)) {
+        for (int q0 = 0; q0 < B; q0 += kTileMaxNB) {
+            const int nq = B - q0 < kTileMaxNB ? B - q0 : kTileMaxNB;
+            const TilePlan tp = tile_plan(V, dtype == VIE_BF16, nq, k);
             const char *hp = hb + (int64_t)q0 * row_bytes;
             int32_t *ip = ids + (int64_t)q0 * k;
             float *lp = logits + (int64_t)q0 * k;
-            hipError_t e =
-                nq <= 16   ? mfma_launch<1, VIE_MFMA_KC1, VIE_MFMA_LA1>(W, V, d, hp, nq, k, mp, zbuf, tops, ip, lp, s)
-                : nq <= 32 ? mfma_launch<2, VIE_MFMA_KC2, VIE_MFMA_LA2>(W, V, d, hp, nq, k, mp, zbuf, tops, ip, lp, s)
-                           : mfma_launch<4, VIE_MFMA_KC4, VIE_MFMA_LA4>(W, V, d, hp, nq, k, mp, zbuf, tops, ip, lp, s);
+            const hipError_t e =
+                dtype == VIE_BF16 ? tile_launch_nq<true>(W, V, row_bytes, hp, nq, k, tp, zbuf, tops, ip, lp, s)
+                                  : tile_launch_nq<false>(W, V, row_bytes, hp, nq, k, tp, zbuf, tops, ip, lp, s);
             if (e != hipSuccess) return launched(e, "dense top-k (matrix cores) launch");
         }
         return VIE_OK;

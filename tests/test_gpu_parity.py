@@ -114,6 +114,43 @@ def test_dense_topk_matches_oracle(vie, V, d, dtype, B, k):
         assert np.array_equal(ids2.cpu().numpy(), ids) and np.array_equal(lg2.cpu().numpy(), lg)
 
 
+@pytest.mark.parametrize("V,d,dtype,B,k", [
+    (33001, 100, synth.F32, 3, 50),    # two row tiles a wave, V not a multiple of 4, 400-byte rows (a tail)
+    (32769, 64, synth.F32, 16, 128),   # one row past one block per workgroup
+    (32768, 36, synth.F32, 17, 129),   # one full block per workgroup; slabs of one block (k above 128)
+    (66000, 20, synth.F32, 33, 10),    # several blocks, 80-byte rows, four query tiles padded
+    (66000, 24, synth.BF16, 64, 300),  # several blocks and slabs per workgroup
+    (70001, 136, synth.BF16, 7, 100),  # two row tiles, a ragged last block, scalar logit stores
+    (300, 516, synth.F32, 64, 100),    # a few rows per workgroup
+    (5, 4, synth.F32, 3, 5),           # one 16-byte piece per row, two workgroups
+])
+def test_dense_batches_on_the_matrix_cores(vie, V, d, dtype, B, k):
+    say("dense batch", V, d, dtype, B, k)
+    W = synth.make_w(V, d, dtype, 41 + V)
+    H, _ = synth.make_queries(W, dtype, B, 42 + V)
+    ids, lg = vie.DenseHead(dev_tensor(vie, W, dtype), max_batch=B, max_k=k)(dev_tensor(vie, H, dtype), k)
+    torch.cuda.synchronize()
+    ids, lg = ids.cpu().numpy(), lg.cpu().numpy()
+    oid, olg, osc = O.topk(W, dtype, H, k)
+    parity.check_logits(W, dtype, H, ids, lg, "dense batch")
+    parity.check_id_sets(W, dtype, H, ids, oid, osc[:, -1], what="dense batch")
+
+
+@pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
+def test_dense_batch_keeps_nonfinite_values_in_their_rows(vie, dtype):
+    # rows that end inside a stage: an infinity in a row's last piece reaches
+    # that row's logits only, as infinity, not the zeros past the row
+    V, d, B = 3000, 72, 4
+    W = synth.make_w(V, d, dtype, 61)
+    H, _ = synth.make_queries(W, dtype, B, 62)
+    Wd = dev_tensor(vie, W, dtype).clone()
+    Hd = dev_tensor(vie, H, dtype).abs()
+    Wd[1234, d - 1] = float("inf")
+    ids, lg = vie.DenseHead(Wd, max_batch=B, max_k=20)(Hd, 20)
+    torch.cuda.synchronize()
+    assert (ids[:, 0] == 1234).all() and torch.isinf(lg[:, 0]).all() and torch.isfinite(lg[:, 1:]).all()
+
+
 @pytest.mark.parametrize("B,k", [(1, 50), (1, 100), (16, 50), (16, 100)])
 def test_dense_far_maximum_takes_the_exact_fallbacks(vie, B, k):
     # one planted row per query scores about 2^20 times the usual maximum, so
