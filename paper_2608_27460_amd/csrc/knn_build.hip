@@ -45,9 +45,6 @@ constexpr int kDigitBuckets = 1 << kDigitBits;
 constexpr int kGatherCap = 2048;             // keys a selection sorts in LDS
 constexpr int kSelectThreads = 256;
 constexpr int kSelectRows = 128;             // candidate rows of one Gram block (K <= 128)
-constexpr int kChunkBytes = 256;             // bytes of a row per staged chunk
-constexpr int kChunkPitch = kChunkBytes + 32;  // padded: the matrix-core operand reads hit every LDS bank once
-constexpr int kGramPitch = kSelectRows + 1;  // floats per Gram row in LDS
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -854,40 +851,88 @@ __device__ __forceinline__ float dot16(u32x4 a, u32x4 b, float acc, bool bf16)
     return fmaf(__uint_as_float(a3), __uint_as_float(b3), acc);
 }
 
-constexpr size_t kSelectBig = (size_t)kSelectRows * kChunkPitch > (size_t)kSelectRows * kGramPitch * 4
-                                   ? (size_t)kSelectRows * kChunkPitch
-                                   : (size_t)kSelectRows * kGramPitch * 4;
-constexpr size_t kSelectLds = kSelectBig + (size_t)kSelectRows * 8 + 256 * 4;
+// Step 2, one workgroup per node: the products of its candidates with each
+// other, then the heuristic scan in candidate order by one wave.  A node with
+// at most M0 candidates keeps them all.
+//
+// The scan reads the product of e with an r kept before it only, so of the
+// 8 x 8 tiles of 16 x 16 the 36 on and below the diagonal are multiplied,
+// nine a wave, fp32 accumulation (the layout of knn_gram_kernel).  Bound by
+// the gather of K rows per node through the caches (40 GB a build at 151936 x
+// 1024 bf16), so what counts is bytes in flight: stages of kSelKC bytes of
+// each candidate go straight to LDS (global_load_lds, 16 bytes a lane), two
+// ahead, and the products are kept as a packed triangle over the spent
+// stages, so that three workgroups fit a CU.  151936 x 1024 bf16: 4.9 ms (8.2
+// TB/s of gathered rows); all 64 tiles from register-staged rows, two
+// workgroups a CU and a scan that read one product at a time took 11.2.
+// 32768 x 256 fp32: 1.8 ms on the matrix cores (in the sums' order of the
+// scores they are compared with), 4.8 on the vector ALUs.
+constexpr int kSelKC = 128;       // bytes of a row per stage
+constexpr int kSelBufs = 3;
+constexpr int kSelStage = kSelectRows * kSelKC;
+constexpr int kSelTiles = kSelectRows / 16;
+constexpr int kSelWaves = kSelectThreads / kWave;
+constexpr int kSelOwn = kSelTiles * (kSelTiles + 1) / 2 / kSelWaves;  // tiles of a wave
+static_assert(kSelOwn * kSelWaves * 2 == kSelTiles * (kSelTiles + 1), "tiles divide evenly over the waves");
+constexpr int kSelLoads = kSelStage / (16 * kSelectThreads);
+constexpr int kSelTri = kSelectRows * (kSelectRows + 1) / 2 * 4;
+static_assert(kSelTri <= kSelBufs * kSelStage, "the triangle takes the place of the stages");
+constexpr size_t kSelectLds = (size_t)kSelBufs * kSelStage + (size_t)kSelectRows * 8;
 
-// Step 2, one workgroup per node: the Gram matrix of its candidates (rows
-// staged through LDS in chunks of kChunkBytes, fp32 accumulation; matrix
-// cores for bf16 rows, vector ALUs for fp32 rows), then the heuristic scan
-// in candidate order by one wave.  A node with at most M0 candidates keeps
-// them all.
+// Staged row x holds its 16-byte piece p at p ^ ((x >> 1) & 7): the operand
+// reads (16 rows, one piece each of four) hit every LDS bank once.
+__device__ __forceinline__ int sel_piece(int x, int p) { return x * kSelKC + ((p ^ ((x >> 1) & 7)) << 4); }
+
+// Wave w's tiles: block rows w and 7 - w of the lower triangle, (w + 1) +
+// (8 - w) = 9 tiles; its tile t is (m, n) with n <= m.
+__device__ __forceinline__ int sel_m(int w, int t) { return t <= w ? w : kSelTiles - 1 - w; }
+__device__ __forceinline__ int sel_n(int w, int t) { return t <= w ? t : t - w - 1; }
+
+// Adds a stage's products to the nine tiles of wave W.
+template <bool BF16, int W> __device__ __forceinline__ void sel_multiply(const char *buf, int r, int g, f32x4 (&acc)[kSelOwn])
+{
+    constexpr int NX = kSelTiles - W;  // operands: block rows 0 .. 7 - W (row w of the pair is among them)
+    if constexpr (BF16) {
+#pragma unroll
+        for (int kk = 0; kk < kSelKC / 64; ++kk) {  // 32 columns per step
+            u32x4 x[NX];
+#pragma unroll
+            for (int n = 0; n < NX; ++n) x[n] = *reinterpret_cast<const u32x4 *>(buf + sel_piece(16 * n + r, 4 * kk + g));
+#pragma unroll
+            for (int t = 0; t < kSelOwn; ++t) acc[t] = mfma_bf16(x[sel_m(W, t)], x[sel_n(W, t)], acc[t]);
+        }
+    } else {
+#pragma unroll
+        for (int kk = 0; kk < kSelKC / 16; ++kk) {  // 4 columns per step
+            float x[NX];
+#pragma unroll
+            for (int n = 0; n < NX; ++n) x[n] = *reinterpret_cast<const float *>(buf + sel_piece(16 * n + r, kk) + 4 * g);
+#pragma unroll
+            for (int t = 0; t < kSelOwn; ++t) acc[t] = mfma_f32(x[sel_m(W, t)], x[sel_n(W, t)], acc[t]);
+        }
+    }
+}
+
 template <bool BF16>
-__global__ __launch_bounds__(kSelectThreads) void knn_select_kernel(const char *__restrict__ W, int row_bytes,
-                                                                    int K, int M0, const int32_t *__restrict__ cand,
-                                                                    const float *__restrict__ cand_score,
-                                                                    int32_t *__restrict__ fwd,
-                                                                    float *__restrict__ fwd_score,
-                                                                    int32_t *__restrict__ nfwd)
+__global__ __launch_bounds__(kSelectThreads) __attribute__((amdgpu_waves_per_eu(3))) void knn_select_kernel(
+    const char *__restrict__ W, int row_bytes, int K, int M0, const int32_t *__restrict__ cand,
+    const float *__restrict__ cand_score, int32_t *__restrict__ fwd, float *__restrict__ fwd_score,
+    int32_t *__restrict__ nfwd)
 {
     extern __shared__ __align__(16) char smem[];
-    char *tile = smem;                                            // [128][kChunkPitch] staged rows
-    float *G = reinterpret_cast<float *>(smem);                   // [128][kGramPitch] after the tile
-    int32_t *cid = reinterpret_cast<int32_t *>(smem + kSelectBig);  // [128]
-    float *cs = reinterpret_cast<float *>(cid + kSelectRows);     // [128]
-    int32_t *kept = reinterpret_cast<int32_t *>(cs + kSelectRows);  // [<= 256]
+    float *G = reinterpret_cast<float *>(smem);  // packed lower triangle, after the stages
+    int32_t *cid = reinterpret_cast<int32_t *>(smem + kSelBufs * kSelStage);  // [128]
+    float *cs = reinterpret_cast<float *>(cid + kSelectRows);                 // [128]
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int r = lane & 15, g = lane >> 4;
     const int64_t i = blockIdx.x;
-    int nc = 0;
     for (int t = tid; t < kSelectRows; t += kSelectThreads) {
-        const int32_t c = t < K ? cand[i * K + t] : -1;
-        cid[t] = c;
+        cid[t] = t < K ? cand[i * K + t] : -1;
         cs[t] = t < K ? cand_score[i * K + t] : 0.0f;
     }
     __syncthreads();
-    for (int t = 0; t < K; ++t) nc += cid[t] >= 0;  // uniform
+    const int nc = __popcll(__ballot(cid[lane] >= 0)) + __popcll(__ballot(cid[lane + kWave] >= 0));  // uniform
     if (nc <= M0) {
         for (int t = tid; t < M0; t += kSelectThreads) {
             fwd[i * M0 + t] = t < nc ? cid[t] : -1;
@@ -896,122 +941,121 @@ __global__ __launch_bounds__(kSelectThreads) void knn_select_kernel(const char *
         if (tid == 0) nfwd[i] = nc;
         return;
     }
-    // Gram block.  bf16 rows: on the matrix cores, wave w owns the 64 x 64
-    // block (rows 64 (w / 2), columns 64 (w % 2)) as 4 x 4 tiles of
-    // v_mfma_f32_16x16x32_bf16, lane (r, g) supplying columns 8 g .. 8 g + 7
-    // of each 32-column step for row r of a tile.  fp32 rows: on the vector
-    // ALUs, thread (ta, tb) owns pairs (ta + 16 x, tb + 16 y) (rows 16 apart
-    // keep the 16-byte reads of a wave on distinct LDS banks).
-    const int ta = tid / 16, tb = tid % 16;
-    const int wv = tid / kWave, mr = lane & 15, mg = lane >> 4;
-    const int rb = 64 * (wv >> 1), cb = 64 * (wv & 1);
-    constexpr int NX = BF16 ? 1 : 8;
-    float acc[NX][NX];
-    f32x4 macc[4][4];
+    // lane (x, p) of load t brings piece p of staged row x (the place of its
+    // swizzle); past the candidates the first one again, unused
+    const int nfull = row_bytes / kSelKC;
+    const char *src[kSelLoads];
+    int spiece[kSelLoads];
 #pragma unroll
-    for (int x = 0; x < NX; ++x)
+    for (int t = 0; t < kSelLoads; ++t) {
+        const int x = (t * kSelectThreads + tid) / 8;
+        const int32_t c = cid[x];
+        spiece[t] = 16 * ((tid & 7) ^ ((x >> 1) & 7));
+        src[t] = W + (int64_t)(c >= 0 ? c : cid[0]) * row_bytes + spiece[t];
+    }
+    auto issue = [&](int st, int buf) {
+        const int64_t so = (int64_t)min(st, nfull - 1) * kSelKC;  // past the end: the last stage again, unused
 #pragma unroll
-        for (int y = 0; y < NX; ++y) acc[x][y] = 0.0f;
+        for (int t = 0; t < kSelLoads; ++t)
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void *)(src[t] + so),
+                (__attribute__((address_space(3))) void *)(smem + buf * kSelStage + (t * kSelectThreads + wave * kWave) * 16),
+                16, 0, 0);
+    };
+    f32x4 acc[kSelOwn];
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
-#pragma unroll
-        for (int n = 0; n < 4; ++n) macc[m][n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    const u32x4 zero = {0u, 0u, 0u, 0u};
-    // stage 128 rows x 256 bytes per chunk (16 pieces of 16 bytes per row,
-    // kPieces per thread); for bf16 rows the next chunk's pieces load into
-    // registers while the current one is multiplied
-    constexpr int kPieces = kSelectRows * (kChunkBytes / 16) / kSelectThreads;
-    static_assert(kPieces * kSelectThreads == kSelectRows * (kChunkBytes / 16), "staging shape");
-    u32x4 pre[kPieces];
-    auto load_chunk = [&](int c0) {
-#pragma unroll
-        for (int j = 0; j < kPieces; ++j) {
-            const int p = tid + j * kSelectThreads;
-            const int r = p / (kChunkBytes / 16), off = c0 + 16 * (p % (kChunkBytes / 16));
-            const int32_t c = cid[r];
-            pre[j] = c >= 0 && off < row_bytes ? *reinterpret_cast<const u32x4 *>(W + (int64_t)c * row_bytes + off)
-                                               : zero;
+    for (int t = 0; t < kSelOwn; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    auto multiply = [&](const char *buf) {
+        switch (wave) {  // uniform in a wave
+        case 0: sel_multiply<BF16, 0>(buf, r, g, acc); break;
+        case 1: sel_multiply<BF16, 1>(buf, r, g, acc); break;
+        case 2: sel_multiply<BF16, 2>(buf, r, g, acc); break;
+        default: sel_multiply<BF16, 3>(buf, r, g, acc); break;
         }
     };
-    // (bf16 rows only: fp32 rows hold an 8 x 8 block of sums per thread, and
-    // the extra registers would halve their occupancy)
-    if constexpr (BF16) load_chunk(0);
-    for (int c0 = 0; c0 < row_bytes; c0 += kChunkBytes) {
-        __syncthreads();  // every wave is done with the previous chunk
-        if constexpr (!BF16) load_chunk(c0);
+    static_assert(kSelWaves == 4, "a case per wave");
+    if (nfull > 0) {
 #pragma unroll
-        for (int j = 0; j < kPieces; ++j) {
-            const int p = tid + j * kSelectThreads;
-            *reinterpret_cast<u32x4 *>(tile + (p / (kChunkBytes / 16)) * kChunkPitch + 16 * (p % (kChunkBytes / 16))) =
-                pre[j];
-        }
-        if constexpr (BF16)
-            if (c0 + kChunkBytes < row_bytes) load_chunk(c0 + kChunkBytes);
-        __syncthreads();
-        if constexpr (BF16) {
-#pragma unroll
-            for (int t = 0; t < kChunkBytes / 64; ++t) {  // 32 bf16 columns per step
-                u32x4 a[4], b[4];
-#pragma unroll
-                for (int m = 0; m < 4; ++m)
-                    a[m] = *reinterpret_cast<const u32x4 *>(tile + (rb + 16 * m + mr) * kChunkPitch + 64 * t + 16 * mg);
-#pragma unroll
-                for (int n = 0; n < 4; ++n)
-                    b[n] = *reinterpret_cast<const u32x4 *>(tile + (cb + 16 * n + mr) * kChunkPitch + 64 * t + 16 * mg);
-#pragma unroll
-                for (int m = 0; m < 4; ++m)
-#pragma unroll
-                    for (int n = 0; n < 4; ++n) macc[m][n] = mfma_bf16(a[m], b[n], macc[m][n]);
-            }
-        } else {
-#pragma unroll 2
-            for (int piece = 0; piece < kChunkBytes / 16; ++piece) {
-                u32x4 a[NX], b[NX];
-#pragma unroll
-                for (int x = 0; x < NX; ++x)
-                    a[x] = *reinterpret_cast<const u32x4 *>(tile + (ta + 16 * x) * kChunkPitch + 16 * piece);
-#pragma unroll
-                for (int y = 0; y < NX; ++y)
-                    b[y] = *reinterpret_cast<const u32x4 *>(tile + (tb + 16 * y) * kChunkPitch + 16 * piece);
-#pragma unroll
-                for (int x = 0; x < NX; ++x)
-#pragma unroll
-                    for (int y = 0; y < NX; ++y) acc[x][y] = dot16(a[x], b[y], acc[x][y], false);
-            }
-        }
+        for (int st = 0; st < kSelBufs - 1; ++st) issue(st, st);
     }
+    int slot = 0;  // buffer of stage st
+    for (int st = 0; st < nfull; ++st) {
+        // this wave's loads of stage st have landed (those of the stages
+        // ahead may be in flight) and its reads of stage st - 1 are done;
+        // past the barrier that holds for every wave
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((kSelBufs - 2) * kSelLoads) : "memory");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        issue(st + kSelBufs - 1, slot == 0 ? kSelBufs - 1 : slot - 1);
+        multiply(smem + slot * kSelStage);
+        slot = slot == kSelBufs - 1 ? 0 : slot + 1;
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __syncthreads();
-    if constexpr (BF16) {
-        // lane (r, g) holds rows 4 g + i of tile m against row r of tile n
+    if (row_bytes % kSelKC) {  // the rest of the rows, zeros past it
 #pragma unroll
-        for (int m = 0; m < 4; ++m)
-#pragma unroll
-            for (int n = 0; n < 4; ++n)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) G[(rb + 16 * m + 4 * mg + e) * kGramPitch + cb + 16 * n + mr] = macc[m][n][e];
-    } else {
-#pragma unroll
-        for (int x = 0; x < NX; ++x)
-#pragma unroll
-            for (int y = 0; y < NX; ++y) G[(ta + 16 * x) * kGramPitch + tb + 16 * y] = acc[x][y];
+        for (int t = 0; t < kSelLoads; ++t) {
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if (nfull * kSelKC + spiece[t] < row_bytes) v = *reinterpret_cast<const u32x4 *>(src[t] + nfull * kSelKC);
+            *reinterpret_cast<u32x4 *>(smem + (t * kSelectThreads + tid) * 16) = v;
+        }
+        __syncthreads();
+        multiply(smem);
+        __syncthreads();
     }
+    // lane (r, g) holds rows 4 g + x of a tile, column r
+#pragma unroll
+    for (int t = 0; t < kSelOwn; ++t)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const int e = 16 * sel_m(wave, t) + 4 * g + x, c = 16 * sel_n(wave, t) + r;
+            if (c <= e) G[e * (e + 1) / 2 + c] = acc[t][x];
+        }
     __syncthreads();
     if (tid < kWave) {
-        // heuristic scan: e is kept iff s_e > <w_e, w_r> for every kept r
+        // heuristic scan: e is kept iff s_e > <w_e, w_r> for every kept r.
+        // Lane l holds candidates l and l + 64; their products with the next
+        // kScan candidates are read together, before it is known which are
+        // kept (entries past e belong to no kept candidate).
+        constexpr int kScan = 8;
+        const float s0 = cs[lane], s1 = cs[lane + kWave];
+        uint64_t k0 = 0ull, k1 = 0ull;  // kept candidates 0 .. 63, 64 .. 127
         int nk = 0;
-        for (int e = 0; e < nc && nk < M0; ++e) {
-            const float se = cs[e];
-            bool bad = false;
-            for (int r = lane; r < nk; r += kWave) bad |= G[e * kGramPitch + kept[r]] >= se;
-            if (!__any(bad)) {
-                if (lane == 0) kept[nk] = e;
-                ++nk;
-                __builtin_amdgcn_wave_barrier();
+        for (int e0 = 0; e0 < nc && nk < M0; e0 += kScan) {
+            float a[kScan], b[kScan];
+#pragma unroll
+            for (int u = 0; u < kScan; ++u) {
+                const float *row = G + (e0 + u) * (e0 + u + 1) / 2;
+                a[u] = row[lane];
+                b[u] = row[lane + kWave];
+            }
+#pragma unroll
+            for (int u = 0; u < kScan; ++u) {
+                const int e = e0 + u;
+                const float se = __uint_as_float((uint32_t)__builtin_amdgcn_readlane(
+                    (int)__float_as_uint(e0 < kWave ? s0 : s1), e & (kWave - 1)));
+                const uint64_t bad = (__ballot(a[u] >= se) & k0) | (__ballot(b[u] >= se) & k1);
+                if (bad == 0ull && e < nc && nk < M0) {
+                    if (e0 < kWave) k0 |= 1ull << (e & (kWave - 1));
+                    else k1 |= 1ull << (e & (kWave - 1));
+                    ++nk;
+                }
             }
         }
-        for (int t = lane; t < M0; t += kWave) {
-            fwd[i * M0 + t] = t < nk ? cid[kept[t]] : -1;
-            fwd_score[i * M0 + t] = t < nk ? cs[kept[t]] : 0.0f;
+        const uint64_t below = (1ull << lane) - 1ull;
+        const int p0 = __popcll(k0 & below), p1 = __popcll(k0) + __popcll(k1 & below);
+        if (k0 >> lane & 1ull) {
+            fwd[i * M0 + p0] = cid[lane];
+            fwd_score[i * M0 + p0] = s0;
+        }
+        if (k1 >> lane & 1ull) {
+            fwd[i * M0 + p1] = cid[lane + kWave];
+            fwd_score[i * M0 + p1] = s1;
+        }
+        for (int t = nk + lane; t < M0; t += kWave) {
+            fwd[i * M0 + t] = -1;
+            fwd_score[i * M0 + t] = 0.0f;
         }
         if (lane == 0) nfwd[i] = nk;
     }

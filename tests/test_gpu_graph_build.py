@@ -78,6 +78,23 @@ def test_integer_rows_give_the_oracle_graph(vie, tmp_path, V, d, dtype, K, M0, c
     assert open(pg, "rb").read() == open(po, "rb").read()
 
 
+@pytest.mark.parametrize("V,d,dtype,K,M0", [
+    (400, 8, synth.BF16, 17, 16),    # 16-byte rows: no whole stage; one candidate too many
+    (400, 64, synth.BF16, 128, 2),   # exactly one stage; the scan stops early
+    (400, 72, synth.BF16, 65, 8),    # a stage and 16 bytes; one candidate in the upper half
+    (300, 136, synth.BF16, 127, 100),
+    (300, 4, synth.F32, 16, 3),      # a tile of candidates
+    (500, 36, synth.F32, 128, 127),  # a stage and 16 bytes of fp32
+    (260, 128, synth.F32, 64, 63),   # four whole stages
+])
+def test_selection_at_the_edges_of_its_tiles(vie, V, d, dtype, K, M0):
+    # integer rows: every product and sum is exact, so the lists are the oracle's
+    say("gpu build (selection)", V, d, dtype, K, M0)
+    W = integer_rows(V, d, dtype, V + d)
+    ix, g, _ = build_both(vie, W, dtype, K, M0)
+    assert np.array_equal(ix.export()["adj0"], g.adj0)
+
+
 def test_integer_hub_rows_with_large_reverse_lists(vie):
     # five rows of ten times the norm are near to nearly every row, so each
     # collects thousands of reverse edges (more than one selection round holds)
