@@ -614,65 +614,88 @@ __global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(4,
 }
 
 // Threshold of each row of a chunk from its scores against the sampled rows
-// (sampled row p is row p * step of W_out): the want-th largest, the row
-// itself left out.  A histogram of the scores' top bits finds the bucket it
-// falls in, and the keys from that bucket up are ranked (more than kGatherCap
-// of them: the bucket's lower edge, still a valid threshold).
-__global__ __launch_bounds__(kTopkThreads) void knn_threshold_kernel(const float *__restrict__ S, int64_t ld,
-                                                                     int64_t r0, int64_t np, int step, int want,
-                                                                     float *__restrict__ thr)
+// (sampled row p is row p * step of W_out): the want-th largest (want <= 64),
+// the row itself left out.  One wave per row, no barrier: the want-th largest
+// of the 64 lanes' maxima has at least `want` scores at or above it; those
+// are listed and ranked (more than kThrCap of them, equal scores: that bound
+// itself, still a valid threshold).  Bound by its two reads of the scores, the
+// second from the caches: 151936 rows of 4748 scores take 1.0 ms (2.9 GB); a
+// histogram of a row in LDS, whose updates meet in a few buckets, took 3.25.
+constexpr int kThrWaves = 4;
+constexpr int kThrCap = 512;
+
+__global__ __launch_bounds__(kThrWaves *kWave) void knn_threshold_kernel(const float *__restrict__ S, int64_t ld,
+                                                                        int64_t r0, int64_t rows, int64_t np, int step,
+                                                                        int want, float *__restrict__ thr)
 {
-    __shared__ TopkShared sh;
-    const int tid = threadIdx.x;
-    const int64_t i = r0 + blockIdx.x;
-    const float *row = S + (int64_t)blockIdx.x * ld;
-    for (int b = tid; b < kDigitBuckets; b += kTopkThreads) sh.hist[b] = 0u;
-    if (tid == 0) {
-        sh.n = 0u;
-        sh.count = 0u;
-        thr[i] = -__builtin_inff();
-    }
-    __syncthreads();
-    for (int64_t p = tid; p < np; p += kTopkThreads)
-        if (p * step != i) atomicAdd(&sh.hist[f2ord(row[p]) >> (32 - kDigitBits)], 1u);
-    __syncthreads();
-    constexpr int per = kDigitBuckets / kTopkThreads;
-    uint32_t c[per], sum = 0;
+    __shared__ uint32_t s_list[kThrWaves][kThrCap];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int64_t rr = (int64_t)blockIdx.x * kThrWaves + wave;
+    if (rr >= rows) return;
+    const int64_t i = r0 + rr;
+    const int64_t self = i % step == 0 ? i / step : -1;  // the row's own place in the sample
+    const f32x4 *row = reinterpret_cast<const f32x4 *>(S + rr * ld);  // (rows of scores start 16-byte aligned)
+    const int64_t n4 = (np + 3) / 4;  // scores past np are in the row's padding, left out below
+    // order bits of the scores 4 c .. 4 c + 3 (0 for those left out: no score has these bits but a NaN)
+    auto bits = [&](int64_t c, uint32_t(&o)[4]) {
+        const f32x4 v = row[c];
 #pragma unroll
-    for (int j = 0; j < per; ++j) {
-        c[j] = sh.hist[kDigitBuckets - 1 - (per * tid + j)];
-        sum += c[j];
-    }
-    uint32_t above = block_exclusive_scan<kTopkThreads>(sum, sh.wsum);
-#pragma unroll
-    for (int j = 0; j < per; ++j) {
-        if (above < (uint32_t)want && (uint32_t)want <= above + c[j]) {
-            sh.bucket = (uint32_t)(kDigitBuckets - 1 - (per * tid + j));
-            sh.count = 1u;
+        for (int x = 0; x < 4; ++x) {
+            const int64_t p = 4 * c + x;
+            o[x] = p < np && p != self ? f2ord(v[x]) : 0u;
         }
-        above += c[j];
+    };
+    uint32_t mx = 0u;
+#pragma unroll 4
+    for (int64_t c = lane; c < n4; c += kWave) {
+        uint32_t o[4];
+        bits(c, o);
+        mx = max(mx, max(max(o[0], o[1]), max(o[2], o[3])));
     }
-    __syncthreads();
-    if (sh.count == 0u) return;  // fewer sampled scores than wanted: no threshold
-    const uint32_t edge = sh.bucket << (32 - kDigitBits);
-    for (int64_t p = tid; p < np; p += kTopkThreads) {
-        const uint32_t o = f2ord(row[p]);
-        if (o >= edge && p * step != i) {
-            const uint32_t slot = atomicAdd(&sh.n, 1u);
-            if (slot < (uint32_t)kGatherCap) sh.gat[slot] = ((uint64_t)o << 32) | (uint32_t)p;
+    // the want-th largest lane maximum
+    uint32_t lo = 0u;
+    {
+        int above = 0, equal = 0;
+        for (int l = 0; l < kWave; ++l) {
+            const uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)mx, l);
+            above += m > mx;
+            equal += m == mx;
         }
+        const uint64_t at = __ballot(above < want && want <= above + equal);  // (never empty: want <= 64)
+        lo = (uint32_t)__builtin_amdgcn_readlane((int)mx, __ffsll((long long)at) - 1);
     }
-    __syncthreads();
-    const int m = (int)sh.n;
-    if (m > kGatherCap) {
-        if (tid == 0) thr[i] = ord2f(edge);
+    if (lo == 0u) {  // fewer lanes with a score than wanted: no threshold
+        if (lane == 0) thr[i] = -__builtin_inff();
         return;
     }
-    for (int t = tid; t < m; t += kTopkThreads) {
-        const uint64_t key = sh.gat[t];
-        int rank = 0;
-        for (int u = 0; u < m; ++u) rank += sh.gat[u] > key;
-        if (rank == want - 1) thr[i] = ord2f((uint32_t)(key >> 32));
+    uint32_t *list = s_list[wave];
+    uint32_t m = 0;
+    for (int64_t c0 = 0; c0 < n4; c0 += kWave) {
+        uint32_t o[4] = {0u, 0u, 0u, 0u};
+        if (c0 + lane < n4) bits(c0 + lane, o);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const uint64_t hit = __ballot(o[x] >= lo);
+            if (hit == 0ull) continue;
+            const uint32_t at = m + __builtin_amdgcn_mbcnt_hi((uint32_t)(hit >> 32),
+                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)hit, 0u));
+            if (o[x] >= lo && at < (uint32_t)kThrCap) list[at] = o[x];
+            m += (uint32_t)__popcll(hit);
+        }
+    }
+    if (m > (uint32_t)kThrCap) {
+        if (lane == 0) thr[i] = ord2f(lo);
+        return;
+    }
+    __builtin_amdgcn_wave_barrier();
+    for (uint32_t t = lane; t < m; t += kWave) {
+        const uint32_t v = list[t];
+        int above = 0, equal = 0;
+        for (uint32_t u = 0; u < m; ++u) {
+            above += list[u] > v;
+            equal += list[u] == v;
+        }
+        if (above < want && want <= above + equal) thr[i] = ord2f(v);  // (equal scores write the same)
     }
 }
 
@@ -1305,12 +1328,14 @@ vie_status build_knn_graph_gpu(const void *W_dev, int dtype, int64_t V, int d, i
         const int64_t pld = (npick + 3) & ~(int64_t)3;
         const int64_t PR = std::min<int64_t>(V, (int64_t)(score_bytes / (pld * 4)));
         const double mean = (double)K * npick / V;
-        const int want = (int)std::ceil(mean + 3.5 * std::sqrt(mean) + 2.0);
+        // (at most 55: from kPairMinRows rows on at most one row in four is sampled)
+        const int want = std::min(kWave, (int)std::ceil(mean + 3.5 * std::sqrt(mean) + 2.0));
         for (int64_t r0 = 0; r0 < V && he == hipSuccess; r0 += PR) {
             const int64_t rows = std::min(PR, V - r0);
             he = launch_gram(nullptr, r0, rows, b.pick, npick, pld);
             if (he != hipSuccess) break;
-            knn_threshold_kernel<<<(unsigned)rows, kTopkThreads, 0, s>>>(b.S, pld, r0, npick, pick_step, want, b.thr);
+            knn_threshold_kernel<<<(unsigned)((rows + kThrWaves - 1) / kThrWaves), kThrWaves * kWave, 0, s>>>(
+                b.S, pld, r0, rows, npick, pick_step, want, b.thr);
             he = hipGetLastError();
         }
         if (he == hipSuccess) he = hipMemsetAsync(b.count, 0, (size_t)V * 4, s);
