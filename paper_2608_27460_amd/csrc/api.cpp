@@ -72,20 +72,25 @@ vie_status check_k(int32_t k, int64_t V, int32_t B)
     return VIE_OK;
 }
 
+// A GPU-built index's layer-0 lists copied to host memory.
+vie_status copy_device_adjacency(const vie_index *ix, int32_t *dst)
+{
+    int cur = 0;
+    hipError_t e = hipGetDevice(&cur);
+    if (e == hipSuccess) e = hipSetDevice(ix->dev.device);
+    if (e == hipSuccess) e = hipMemcpy(dst, ix->dev.adj0, (size_t)ix->g.V * ix->g.M0 * 4, hipMemcpyDeviceToHost);
+    (void)hipSetDevice(cur);
+    return e == hipSuccess ? VIE_OK : hip_fail(e, "copying the graph to the host");
+}
+
 // The host copy of a GPU-built index's layer-0 lists (see vie_index).
 vie_status fetch_host_adjacency(vie_index *ix)
 {
     std::lock_guard<std::mutex> lock(ix->host_mu);
     if (!ix->adj0_device_only) return VIE_OK;
-    Graph &g = ix->g;
-    std::vector<int32_t> adj((size_t)g.V * g.M0);
-    int cur = 0;
-    hipError_t e = hipGetDevice(&cur);
-    if (e == hipSuccess) e = hipSetDevice(ix->dev.device);
-    if (e == hipSuccess) e = hipMemcpy(adj.data(), ix->dev.adj0, adj.size() * 4, hipMemcpyDeviceToHost);
-    (void)hipSetDevice(cur);
-    if (e != hipSuccess) return hip_fail(e, "copying the graph to the host");
-    g.adj0.swap(adj);
+    std::vector<int32_t> adj((size_t)ix->g.V * ix->g.M0);
+    if (vie_status s = copy_device_adjacency(ix, adj.data())) return s;
+    ix->g.adj0.swap(adj);
     ix->adj0_device_only = false;
     return VIE_OK;
 }
@@ -267,10 +272,15 @@ vie_status vie_index_export(const vie_index *ix, uint8_t *levels, int32_t *adj0,
 {
     g_last_error.clear();
     if (!ix) return fail(VIE_EINVAL, "NULL index");
-    if (vie_status s = fetch_host_adjacency(const_cast<vie_index *>(ix))) return s;
     const Graph &g = ix->g;
+    if (adj0) {
+        // lists that are only on the device go straight to the caller: a host
+        // copy of the index's own would be made for nothing else
+        std::lock_guard<std::mutex> lock(const_cast<vie_index *>(ix)->host_mu);
+        if (!ix->adj0_device_only) std::memcpy(adj0, g.adj0.data(), g.adj0.size() * 4);
+        else if (vie_status s = copy_device_adjacency(ix, adj0)) return s;
+    }
     if (levels) std::memcpy(levels, g.levels.data(), g.levels.size());
-    if (adj0) std::memcpy(adj0, g.adj0.data(), g.adj0.size() * 4);
     if (upper_off) std::memcpy(upper_off, g.upper_off.data(), g.upper_off.size() * 4);
     if (upper && !g.upper.empty()) std::memcpy(upper, g.upper.data(), g.upper.size() * 4);
     return VIE_OK;

@@ -1211,7 +1211,11 @@ __global__ __launch_bounds__(kEntryThreads) void knn_entry_kernel(const char *__
     }
 }
 
+// The build's scratch (one allocation: hipMalloc and hipFree of a buffer each
+// cost host time that the device spends idle) and the graph the index keeps.
 struct Buffers {
+    void *scratch = nullptr;
+    size_t bytes = 0;  // of scratch, while its parts are laid out
     float *S = nullptr;
     int32_t *cand = nullptr, *fwd = nullptr, *nfwd = nullptr, *adj0 = nullptr, *upper_off = nullptr,
             *upper = nullptr;
@@ -1225,22 +1229,16 @@ struct Buffers {
     float *thr = nullptr;    // threshold of every row
     uint32_t *nleft = nullptr;
     int32_t *left = nullptr;  // rows whose threshold did not serve
+    // a part of n bytes at the end of the scratch (256-byte aligned)
+    template <typename T> void part(T *&p, size_t n)
+    {
+        p = reinterpret_cast<T *>(static_cast<char *>(scratch) + bytes);
+        bytes += (n + 255) & ~(size_t)255;
+    }
     void release()
     {
-        void *p[] = {S, cand, fwd, nfwd, cand_score, fwd_score, count, roff, rev, best, sample, pick, thr, nleft, left};
-        for (void *q : p)
-            if (q) (void)hipFree(q);
-        S = nullptr;
-        cand = fwd = nfwd = nullptr;
-        cand_score = fwd_score = nullptr;
-        count = nullptr;
-        roff = nullptr;
-        rev = nullptr;
-        best = nullptr;
-        sample = pick = nullptr;
-        thr = nullptr;
-        nleft = nullptr;
-        left = nullptr;
+        if (scratch) (void)hipFree(scratch);
+        scratch = nullptr;
     }
     void release_graph()
     {
@@ -1295,15 +1293,32 @@ vie_status build_knn_graph_gpu(const void *W_dev, int dtype, int64_t V, int d, i
     // the rows the thresholds are sampled from: every pick_step-th
     const int pick_step = (int)std::max<int64_t>(1, std::min<int64_t>(kPairPickStep, V / kPairPickRows));
     const int64_t npick = (V + pick_step - 1) / pick_step;
-    if (!dalloc(b.S, score_bytes) || !dalloc(b.cand, (size_t)V * K * 4) ||
-        !dalloc(b.cand_score, (size_t)V * K * 4) || !dalloc(b.fwd, (size_t)edges * 4) ||
-        !dalloc(b.fwd_score, (size_t)edges * 4) || !dalloc(b.nfwd, (size_t)V * 4) ||
-        !dalloc(b.count, (size_t)V * 4) || !dalloc(b.roff, (size_t)(V + 1) * 8) ||
-        !dalloc(b.rev, (size_t)edges * 8) || !dalloc(b.best, 8) || !dalloc(b.adj0, (size_t)edges * 4) ||
-        !dalloc(b.upper_off, (size_t)V * 4) || !dalloc(b.upper, 4) ||
-        !dalloc(b.sample, (size_t)(nreg + 1) * row_bytes) ||
-        (pairs && (!dalloc(b.pick, (size_t)npick * row_bytes) || !dalloc(b.thr, (size_t)V * 4) ||
-                   !dalloc(b.nleft, 4) || !dalloc(b.left, (size_t)V * 4)))) {
+    // laid out twice: for the size, then in the allocation
+    auto lay_out = [&]() {
+        b.bytes = 0;
+        b.part(b.S, score_bytes);
+        b.part(b.cand, (size_t)V * K * 4);
+        b.part(b.cand_score, (size_t)V * K * 4);
+        b.part(b.fwd, (size_t)edges * 4);
+        b.part(b.fwd_score, (size_t)edges * 4);
+        b.part(b.nfwd, (size_t)V * 4);
+        b.part(b.count, (size_t)V * 4);
+        b.part(b.roff, (size_t)(V + 1) * 8);
+        b.part(b.rev, (size_t)edges * 8);
+        b.part(b.best, 8);
+        b.part(b.sample, (size_t)(nreg + 1) * row_bytes);
+        if (pairs) {
+            b.part(b.pick, (size_t)npick * row_bytes);
+            b.part(b.thr, (size_t)V * 4);
+            b.part(b.nleft, 4);
+            b.part(b.left, (size_t)V * 4);
+        }
+    };
+    lay_out();
+    bool ok = dalloc(b.scratch, b.bytes);
+    if (ok) lay_out();
+    ok = ok && dalloc(b.adj0, (size_t)edges * 4) && dalloc(b.upper_off, (size_t)V * 4) && dalloc(b.upper, 4);
+    if (!ok) {
         b.release();
         b.release_graph();
         return fail(VIE_ENOMEM, "GPU build: device allocation failed (V = %lld, chunk of %lld rows)", (long long)V,
@@ -1314,6 +1329,36 @@ vie_status build_knn_graph_gpu(const void *W_dev, int dtype, int64_t V, int d, i
         b.release();
         b.release_graph();
         return st;
+    };
+
+    // the sampled rows of W_out gathered on the device (one strided copy
+    // and the last row), then one copy to the host: a copy per row, or a
+    // strided copy straight to host memory, took 7-15 ms of host time.  They
+    // come first so that they are hashed while the device works.
+    std::vector<char> sample((size_t)(nreg + 1) * row_bytes);
+    he = hipMemcpy2DAsync(b.sample, (size_t)row_bytes, W_dev, (size_t)step * row_bytes, (size_t)row_bytes, (size_t)nreg,
+                          hipMemcpyDeviceToDevice, s);
+    if (he == hipSuccess)
+        he = hipMemcpyAsync(b.sample + nreg * row_bytes, static_cast<const char *>(W_dev) + (V - 1) * row_bytes,
+                            row_bytes, hipMemcpyDeviceToDevice, s);
+    if (he == hipSuccess) he = hipMemcpyAsync(sample.data(), b.sample, sample.size(), hipMemcpyDeviceToHost, s);
+    if (he == hipSuccess) he = hipStreamSynchronize(s);
+    if (he != hipSuccess) return bail(fail(VIE_EHIP, "GPU build: %s", hipGetErrorString(he)));
+    // host form of the graph (the index file and vie_index_export read it),
+    // made while the device works
+    auto host_part = [&]() {
+        g = Graph();
+        g.V = V;
+        g.d = d;
+        g.dtype = dtype;
+        g.M0 = M0;
+        g.M = std::min(M0, std::max(2, M0 / 2));
+        g.efC = K;
+        g.seed = 0;
+        g.maxlevel = 0;
+        g.levels.assign((size_t)V, 0);
+        g.upper_off.assign((size_t)V, -1);
+        g.fingerprint = w_fingerprint_rows(sample.data(), dtype, V, d, nreg + 1);
     };
 
     const int64_t gram_nj4 = ((V + kGramTile - 1) / kGramTile + 3) / 4 * 4;  // tiles of j, rounded up to 4
@@ -1380,6 +1425,7 @@ vie_status build_knn_graph_gpu(const void *W_dev, int dtype, int64_t V, int d, i
             knn_pick_kernel<<<(unsigned)V, kTopkThreads, 0, s>>>(K, b.count, keys, b.cand, b.cand_score, b.nleft, b.left);
             he = hipGetLastError();
         }
+        if (he == hipSuccess) host_part();
         if (he == hipSuccess) he = hipMemcpyAsync(&nleft, b.nleft, 4, hipMemcpyDeviceToHost, s);
         if (he == hipSuccess) he = hipStreamSynchronize(s);
         if (he == hipSuccess && nleft > 0) he = chunked(b.left, nleft);
@@ -1412,37 +1458,14 @@ vie_status build_knn_graph_gpu(const void *W_dev, int dtype, int64_t V, int d, i
     if (he == hipSuccess) he = hipGetLastError();
     if (he != hipSuccess) return bail(fail(VIE_EHIP, "GPU build: %s", hipGetErrorString(he)));
 
-    // host form of the graph (the index file and vie_index_export read it)
-    g = Graph();
-    g.V = V;
-    g.d = d;
-    g.dtype = dtype;
-    g.M0 = M0;
-    g.M = std::min(M0, std::max(2, M0 / 2));
-    g.efC = K;
-    g.seed = 0;
-    g.maxlevel = 0;
-    g.levels.assign((size_t)V, 0);
-    g.upper_off.assign((size_t)V, -1);
     // (the layer-0 lists stay on the device: the index copies them to the
     // host when a host-side call first needs them)
+    if (!pairs) host_part();
     unsigned long long best = 0;
     he = hipMemcpyAsync(&best, b.best, 8, hipMemcpyDeviceToHost, s);
-    // the sampled rows of W_out gathered on the device (one strided copy
-    // and the last row), then one copy to the host: a copy per row, or a
-    // strided copy straight to host memory, took 7-15 ms of host time
-    std::vector<char> sample((size_t)(nreg + 1) * row_bytes);
-    if (he == hipSuccess)
-        he = hipMemcpy2DAsync(b.sample, (size_t)row_bytes, W_dev, (size_t)step * row_bytes, (size_t)row_bytes,
-                              (size_t)nreg, hipMemcpyDeviceToDevice, s);
-    if (he == hipSuccess)
-        he = hipMemcpyAsync(b.sample + nreg * row_bytes, static_cast<const char *>(W_dev) + (V - 1) * row_bytes,
-                            row_bytes, hipMemcpyDeviceToDevice, s);
-    if (he == hipSuccess) he = hipMemcpyAsync(sample.data(), b.sample, sample.size(), hipMemcpyDeviceToHost, s);
     if (he == hipSuccess) he = hipStreamSynchronize(s);
     if (he != hipSuccess) return bail(fail(VIE_EHIP, "GPU build: %s", hipGetErrorString(he)));
     g.entry = (int32_t)(~(uint32_t)best);
-    g.fingerprint = w_fingerprint_rows(sample.data(), dtype, V, d, nreg + 1);
     b.release();
 
     dg = DeviceGraph();
