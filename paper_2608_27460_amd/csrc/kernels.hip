@@ -1323,6 +1323,8 @@ struct HnswShared {
     // and a wait that gave up
     uint32_t nother;
     int team_err;
+    uint32_t nx;  // keys of the other members at this exchange
+    int nover;    // some member's keys exceed its line
     uint32_t nfetch;  // hnsw_multi_kernel sharing rows: new nodes whose row is fetched
     // hnsw_multi_kernel: the bound below which kept keys cannot enter the beam
     uint32_t fmin, fmax, fsel, fcount, fn, ftau;
@@ -1330,21 +1332,36 @@ struct HnswShared {
 
 // A team: `size` workgroups (a power of two) search one query together
 // (workgroup q * size + m is member m of query q).  Every member keeps the
-// whole search state and takes every decision itself; each scores only the
-// new nodes n with n mod size == m and passes its kept keys to the others through `keys`
-// ([query][3][member][slot] with `slot` entries each) and their number
-// through `tags` ([query][3][member], zero before the launch): at its e-th
-// exchange (from 1) a member publishes (e << 32) | count.  Everything the
-// members pass each other is written with device-scope stores (written
-// through to the device's coherence point) and read with device-scope loads,
-// and a member waits for its own stores to complete before it publishes the
-// count, so no cache needs to be written back or invalidated.
+// whole search state and takes every decision itself; each claims and scores
+// only the new nodes n with n mod size == m and passes its kept keys to the
+// others.  At an exchange a member writes one line of `line` words (a power
+// of two): a header (new nodes scored << 32 | kept keys), then its first
+// line - 1 kept keys, padded.  Bit 31 of every word is the exchange's mark
+// (the id half of a key, ~id with id < 2^31, always has it set): a reader
+// polls each word until it carries the mark, so a line needs no count
+// published after it and no second round trip for its keys.  Only keys
+// beyond the line go to `keys` ([query][2][member][slot], slot words a
+// member) and are complete before the line is written.  Exchanges alternate
+// between two sets of lines and keys and the mark changes with every use of
+// a set, whose lines are zero before the launch: a word shows either this
+// use or the last one, which every member has seen, since every word of a
+// line is written at each use.  Everything the members pass each other is
+// written with device-scope stores (written through to the device's
+// coherence point) and read with device-scope loads, so no cache needs to be
+// written back or invalidated.  An exchange is bound by its round trips: with
+// a count published after the keys had completed, and the keys read after
+// it, and every member claiming every node in its bitmap, a query of the
+// 128256 x 3072 bf16 head (ef 2048, 128 per step, team of 128) took 402 us,
+// now 334; 16 queries on int8 rows of 128256 x 2048 (ef 1024, teams of 16,
+// with forced tokens and scatter) 343 and 305.
 struct TeamArgs {
     int size;
     int slot;
-    uint64_t *keys;
-    uint64_t *tags;
+    int line;
+    uint64_t *keys;   // of a query: keys of set 0, of set 1, then the lines of both sets
 };
+constexpr uint64_t kTeamMark = 1ull << 31;
+constexpr int kTeamWords = 2 * 1024;  // words of a set's lines, at most: two per thread
 
 // Waits of a team member at an exchange are bounded (about two seconds):
 // members are launched only when all of them fit on the device at once, so
@@ -1806,6 +1823,7 @@ constexpr int kKeepFilterMin = 512;
 constexpr int kPickNarrowSpan = 256;  // picks scan: one flag per lane up to this many entries past the first
 constexpr int kMultiHeld = 2;       // rows per group whose lists a group can cache
 constexpr int kClaimBatch = 4;      // list entries a thread claims together
+constexpr int kClaimQuads = 2;      // in a team: quads of entries, where lists are whole quads
 
 // <row a, h> and <row b, h> (b < 0: only a) with both rows' chunks loaded
 // before either is used (chunks past the row's end read as zeros), the
@@ -1977,7 +1995,13 @@ __device__ __forceinline__ float q8_score(int acc, float row_scale, float query_
     return __fmul_rn(a, query_scale);
 }
 
-template <int NT, int VEC, bool BF16, int G, bool Q8, bool SHARE>
+// One form of the kernel per kind of launch, so that no form holds the
+// registers and branches of another: with a team's exchange compiled into all
+// of them, 256 queries sharing rows in pairs (151936 x 1024 bf16, 64 per step)
+// took 1832 us, now 1792, and one query at 8 per step 1.5% longer.
+enum class Form { kOne, kShare, kTeam };
+
+template <int NT, int VEC, bool BF16, int G, bool Q8, Form FORM>
 __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
     const char *__restrict__ W, int64_t V, int row_bytes, const int32_t *__restrict__ adj0, int M0,
     const int32_t *__restrict__ upper_off, const int32_t *__restrict__ upper, int M, int maxlevel, int32_t entry,
@@ -1991,10 +2015,11 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
     __shared__ int32_t s_pick[kMaxWidth];  // this step's picks (beam positions)
     __shared__ int32_t s_np, s_after;
     __shared__ uint32_t s_hmax;           // Q8: bits of max |h|
-    __shared__ uint32_t s_xoff[kMaxTeam + 1];  // team exchange: where each member's keys go
+    __shared__ uint32_t s_xoff[kMaxTeam];  // team exchange: a member's keys beyond its line (place << 16 | count)
     constexpr int kGroups = NT / G;
+    constexpr bool SHARE = FORM == Form::kShare, TEAM = FORM == Form::kTeam;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    const int T = team.size;              // 1: one workgroup per query
+    const int T = TEAM ? team.size : 1;   // workgroups per query
     const int q = blockIdx.x / T, mem = blockIdx.x - q * T;
     uint32_t exchanges = 0;               // team exchanges so far
     const int hbytes = (row_bytes + 15) & ~15;
@@ -2005,10 +2030,11 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
     // t / M0 for t < 2^15 (M0 <= 256) as a multiply-high by this magic number
     const uint32_t m0_magic = (uint32_t)(((1ull << 32) + (uint32_t)M0 - 1u) / (uint32_t)M0);
     const int nid = cap > M ? cap : M;
+    const bool quads = (M0 & 3) == 0;  // lists of whole quads, 16-byte aligned (adj0 is the index's own allocation)
     // list entries a group keeps per lane (as in hnsw_kernel: enough for
     // M0 = 64 at every group width)
     constexpr int PF = G >= 64 ? 1 : G >= 32 ? 2 : kPfbPerLane;
-    const bool cache_on = M0 <= PF * G && T == 1;  // a member scores only its share of the rows
+    const bool cache_on = M0 <= PF * G && !TEAM;  // a member scores only its share of the rows
     const int d = row_bytes / (BF16 ? 2 : 4);
     const int d8 = Q8 ? (d + 15) & ~15 : 0;
     // LDS carve-up (sizes mirror hnsw_multi_lds_bytes)
@@ -2024,7 +2050,7 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
     int32_t *cid = reinterpret_cast<int32_t *>(p);
     p += (size_t)nid * 4;
     int32_t *lcache = reinterpret_cast<int32_t *>(p);  // (none in a team)
-    p += T == 1 ? (size_t)cap * 4 : 0;
+    p += TEAM ? 0 : (size_t)cap * 4;
     int32_t *fid = reinterpret_cast<int32_t *>(p);  // sharing rows: the new nodes whose rows are fetched
     p += SHARE ? (size_t)cap * 4 : 0;
     // flag arrays 8-byte aligned and padded to 8 bytes: the picks scan reads
@@ -2067,7 +2093,7 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
     const int gl = tid % G;
     const int grp = tid / G;
     uint32_t n_dist = 0, n_expand = 0;
-    uint32_t n_other = 0;  // in a team: this thread's claims of nodes another member scores
+    uint32_t n_other = 0;  // in a team: new nodes of the members whose counts this thread reads
     int32_t *trace = trace_all && mem == 0 ? trace_all + (int64_t)q * trace_cap : nullptr;
     // sharing rows: this query's group (queries gq0 .. gq0 + qg - 1) and the launch's epoch
     const int gq0 = SHARE ? q - q % share.size : q;
@@ -2083,74 +2109,82 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
     uint64_t cur = descend_upper<NT, VEC, BF16, G>(W, V, row_bytes, upper_off, upper, M, maxlevel, entry, hs, cid,
                                                    vis, sh, n_dist, n_expand, trace, trace_cap);
 
-    // A team exchange: this member's `mine` keys (already in its slot of
-    // area `area`) meet the other members' keys, appended to dst after the
-    // `*n` already there.  Steps alternate between areas 0 and 1: a member
-    // can only be one exchange ahead of the slowest, so it never overwrites
-    // keys still being read.
-    auto exchange = [&](int area, uint32_t mine, uint64_t *dst, uint32_t *n) {
-        const int64_t base = ((int64_t)q * 3 + area) * T;
-        const uint32_t tag = ++exchanges;
+    // A team exchange: this member's `mine` keys, dst[0 .. mine) (those from
+    // index L - 1 on also in its slot of the exchange's keys), meet the other
+    // members' keys, appended to dst; returns the number of all of them.  The
+    // members' counts of new nodes (`fresh`) go to n_other.  A member can only
+    // be one exchange ahead of the slowest, so it never overwrites what is
+    // still being read.  sh.nx and sh.nover are zero on entry and a barrier
+    // lies behind the writes of dst.
+    const int L = team.line;
+    auto team_keys = [&]() { return team.keys + ((int64_t)q * 3 + (exchanges & 1u)) * T * team.slot; };
+    auto exchange = [&](uint32_t mine, uint32_t fresh, uint64_t *dst) -> int {
+        const uint64_t *keys = team_keys();
+        uint64_t *lines = team.keys + ((int64_t)q * 3 + 2) * T * team.slot + (int64_t)(exchanges & 1u) * T * L;
+        const uint64_t mark = exchanges & 2u ? 0ull : kTeamMark;
+        ++exchanges;
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        __builtin_amdgcn_s_waitcnt(0);  // this wave's key stores are complete
-        __syncthreads();
-        if (tid == 0)
-            __hip_atomic_store(team.tags + base + mem, ((uint64_t)tag << 32) | mine, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-        // wave 0: lane l waits (bounded) for the counts of members l, l + 64,
-        // ..., then the running sums say where each member's keys go
-        constexpr int kPerLane = (kMaxTeam + kWave - 1) / kWave;
-        if (tid < kWave) {
-            uint32_t c[kPerLane];
-            uint32_t need = 0u;  // bit i: the count of member lane + 64 i is still awaited
+        if (mine >= (uint32_t)L) {  // uniform
+            __builtin_amdgcn_s_waitcnt(0);  // this wave's key stores are complete
+            __syncthreads();
+        }
+        for (int w = tid; w < L; w += NT) {
+            uint64_t v = w == 0 ? ((uint64_t)fresh << 32) | mine : w <= (int)mine ? dst[w - 1] & ~kTeamMark : 0ull;
+            __hip_atomic_store(lines + mem * L + w, v | mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        // every thread waits (bounded) for its words of the other members' lines
+        constexpr int kPerThread = kTeamWords / NT;
+        const int lshift = 31 - __builtin_clz((uint32_t)L);
+        uint64_t v[kPerThread];
+        uint32_t need = 0u;
 #pragma unroll
-            for (int i = 0; i < kPerLane; ++i) {
-                c[i] = 0u;
-                const int o = lane + i * kWave;
-                if (o < T && o != mem) need |= 1u << i;
-            }
-            uint32_t spins = 0;
-            while (need) {
+        for (int i = 0; i < kPerThread; ++i) {
+            const int w = tid + i * NT;
+            v[i] = 0ull;
+            if (w < T * L && w >> lshift != mem) need |= 1u << i;
+        }
+        uint32_t spins = 0;
+        while (need) {
 #pragma unroll
-                for (int i = 0; i < kPerLane; ++i)
-                    if (need & (1u << i)) {
-                        const uint64_t w = __hip_atomic_load(team.tags + base + lane + i * kWave, __ATOMIC_RELAXED,
-                                                             __HIP_MEMORY_SCOPE_AGENT);
-                        if ((uint32_t)(w >> 32) == tag) {
-                            c[i] = (uint32_t)w;
-                            need &= ~(1u << i);
-                        }
-                    }
-                if (!need) break;
-                if (++spins > kTeamSpin) {
-                    sh.team_err = 1;
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(1);
-            }
-            uint32_t carry = 0u;
+            for (int i = 0; i < kPerThread; ++i)
+                if (need & (1u << i))
+                    v[i] = __hip_atomic_load(lines + tid + i * NT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-            for (int i = 0; i < kPerLane; ++i) {
-                const uint32_t incl = wave_incl_scan(c[i]) + carry;
-                const int o = lane + i * kWave;
-                if (o < T) s_xoff[o + 1] = incl;
-                carry = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
+            for (int i = 0; i < kPerThread; ++i)
+                if ((v[i] & kTeamMark) == mark) need &= ~(1u << i);
+            if (!need) break;
+            if (++spins > kTeamSpin) {
+                sh.team_err = 1;
+                break;
             }
-            if (lane == 0) s_xoff[0] = 0;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+#pragma unroll
+        for (int i = 0; i < kPerThread; ++i) {
+            const int w = tid + i * NT, o = w >> lshift;
+            if (w >= T * L) continue;
+            if ((w & (L - 1)) == 0) {  // a header (0 for this member)
+                n_other += (uint32_t)(v[i] >> 32);
+                const uint32_t c = (uint32_t)v[i] & 0x7FFFFFFFu;
+                const uint32_t over = c >= (uint32_t)L ? c - (uint32_t)(L - 1) : 0u;
+                s_xoff[o] = over ? atomicAdd(&sh.nx, over) << 16 | over : 0u;
+                if (over) sh.nover = 1;
+            } else if ((uint32_t)v[i] & 0x7FFFFFFFu) {
+                dst[mine + atomicAdd(&sh.nx, 1u)] = v[i] | kTeamMark;
+            }
         }
         __syncthreads();
-        if (sh.team_err) return;
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        const int total = (int)s_xoff[T];
-        for (int j = tid; j < total; j += NT) {
-            int o = 0;  // the member whose keys hold entry j: the last with s_xoff[o] <= j
-            for (int step = kMaxTeam / 2; step > 0; step >>= 1)
-                if (o + step < T && (int)s_xoff[o + step] <= j) o += step;
-            const uint64_t *ok = team.keys + (base + o) * team.slot;
-            dst[mine + j] = __hip_atomic_load(ok + (j - (int)s_xoff[o]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (sh.team_err) return 0;
+        if (sh.nover) {  // uniform: the keys beyond the lines, NT / T threads a member
+            const int per = NT / T, o = tid / per;
+            const uint32_t n = s_xoff[o] & 0xFFFFu, at = mine + (s_xoff[o] >> 16);
+            for (uint32_t i = tid - o * per; i < n; i += per)
+                dst[at + i] = __hip_atomic_load(keys + (int64_t)o * team.slot + (L - 1) + i, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
         }
-        if (tid == 0) *n = mine + (uint32_t)total;
-        __syncthreads();
+        return (int)(mine + sh.nx);
     };
 
     if constexpr (Q8) {  // the layer-0 entry point scored again on its int8 row
@@ -2241,49 +2275,106 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
         // a pick's list comes from the cache slot its flag names while the
         // cache still holds that node's list, else from HBM.  The first slot
         // of each pick marks it expanded (the other bits of its flag stay).
-        // A thread loads its kClaimBatch list entries, marks the picks it
-        // meets expanded, issues all its bitmap claims (an OR of zero where
-        // there is no entry), then appends its new nodes: no claim waits
-        // behind another.
+        // A thread loads its list entries, marks the picks it meets expanded,
+        // issues all its bitmap claims, then appends its new nodes: no claim
+        // waits behind another.  In a team a member claims only the nodes of
+        // its own share: the rest belong to the other members, each of whom
+        // alone needs their bits, and the counts come back with the exchange.
+        // That leaves reading the lists, which a team does 16 bytes a load (a
+        // quarter of the pick, beam and address instructions, and these bound
+        // a phase that all 1024 threads of a CU run).  One workgroup claims
+        // every entry itself and keeps 4-byte reads: in quads 256 queries of
+        // the 151936 x 1024 head at 64 per step took 1835 us against 1816.
         const int ncl = np * M0;
-        for (int t0 = tid; t0 < ncl; t0 += kClaimBatch * NT) {
-            int32_t ev[kClaimBatch];
+        if (TEAM && quads) {
+            for (int b0 = 0; b0 < ncl; b0 += 4 * kClaimQuads * NT) {
+                if (b0 + 4 * (tid & ~(kWave - 1)) >= ncl) break;  // none for this wave
+                int32_t ev[kClaimQuads][4];
 #pragma unroll
-            for (int u = 0; u < kClaimBatch; ++u) {
-                const int t = min(t0 + u * NT, ncl - 1);
-                const int j = (int)__umulhi((uint32_t)t, m0_magic), slot = t - j * M0;
-                const int pj = s_pick[j];
-                const int32_t c = key_id(beam[pj]);
-                const int hint = (int)(flag[pj] >> 1) - 1;
-                const int src = hint >= 0 && lc_id[hint] == c ? hint : -1;
-                // two guarded loads, not one through a selected pointer (that
-                // would be a generic load, which waits on both memory counters)
-                const int32_t ec = src >= 0 ? lcache[max(src, 0) * M0 + slot] : -1;
-                const int32_t eg = src < 0 ? adj0[(int64_t)c * M0 + slot] : -1;
-                ev[u] = t0 + u * NT < ncl ? (src >= 0 ? ec : eg) : -1;
-            }
-#pragma unroll
-            for (int u = 0; u < kClaimBatch; ++u) {
-                const int t = t0 + u * NT;
-                const int j = (int)__umulhi((uint32_t)t, m0_magic);
-                if (t < ncl && t == j * M0) flag[s_pick[j]] |= 1;
-            }
-            uint32_t old[kClaimBatch];
-#pragma unroll
-            for (int u = 0; u < kClaimBatch; ++u)
-                old[u] = atomicOr(&vis[max(ev[u], 0) >> 5], ev[u] >= 0 ? 1u << (ev[u] & 31) : 0u);
-#pragma unroll
-            for (int u = 0; u < kClaimBatch; ++u)
-                if (ev[u] >= 0 && !(old[u] & (1u << (ev[u] & 31)))) {
-                    if ((ev[u] & (T - 1)) == mem) cid[atomicAdd(&sh.nnew, 1u)] = ev[u];
-                    else ++n_other;
+                for (int u = 0; u < kClaimQuads; ++u) {
+                    const int tu = b0 + 4 * (u * NT + tid), t = min(tu, ncl - 4);
+                    const int j = (int)__umulhi((uint32_t)t, m0_magic), slot = t - j * M0;
+                    const int pj = s_pick[j];
+                    const int4 e = *reinterpret_cast<const int4 *>(adj0 + (int64_t)key_id(beam[pj]) * M0 + slot);
+                    const bool in = tu < ncl;
+                    ev[u][0] = in ? e.x : -1;
+                    ev[u][1] = in ? e.y : -1;
+                    ev[u][2] = in ? e.z : -1;
+                    ev[u][3] = in ? e.w : -1;
+                    if (in && slot == 0) flag[pj] |= 1;
                 }
+                uint32_t old[kClaimQuads][4];
+#pragma unroll
+                for (int u = 0; u < kClaimQuads; ++u)
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        const int32_t e = ev[u][x];
+                        old[u][x] = ~0u;
+                        if (e >= 0 && (e & (T - 1)) == mem) old[u][x] = atomicOr(&vis[e >> 5], 1u << (e & 31));
+                    }
+                // one append per wave: the new nodes of each entry position
+                // follow those of the positions before it
+                uint64_t fresh[kClaimQuads][4];
+                uint32_t nf = 0;
+#pragma unroll
+                for (int u = 0; u < kClaimQuads; ++u)
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        fresh[u][x] = __ballot(!(old[u][x] & (1u << (ev[u][x] & 31))));
+                        nf += (uint32_t)__popcll(fresh[u][x]);
+                    }
+                if (nf == 0) continue;
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(&sh.nnew, nf);
+                at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+#pragma unroll
+                for (int u = 0; u < kClaimQuads; ++u)
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        const uint64_t f = fresh[u][x];
+                        if (f >> lane & 1ull)
+                            cid[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(f >> 32),
+                                                               __builtin_amdgcn_mbcnt_lo((uint32_t)f, 0u))] = ev[u][x];
+                        at += (uint32_t)__popcll(f);
+                    }
+            }
+        } else {
+            for (int t0 = tid; t0 < ncl; t0 += kClaimBatch * NT) {
+                int32_t ev[kClaimBatch];
+#pragma unroll
+                for (int u = 0; u < kClaimBatch; ++u) {
+                    const int t = min(t0 + u * NT, ncl - 1);
+                    const int j = (int)__umulhi((uint32_t)t, m0_magic), slot = t - j * M0;
+                    const int pj = s_pick[j];
+                    const int32_t c = key_id(beam[pj]);
+                    const int hint = (int)(flag[pj] >> 1) - 1;
+                    const int src = hint >= 0 && lc_id[hint] == c ? hint : -1;
+                    // two guarded loads, not one through a selected pointer (that
+                    // would be a generic load, which waits on both memory counters)
+                    const int32_t ec = src >= 0 ? lcache[max(src, 0) * M0 + slot] : -1;
+                    const int32_t eg = src < 0 ? adj0[(int64_t)c * M0 + slot] : -1;
+                    ev[u] = t0 + u * NT < ncl ? (src >= 0 ? ec : eg) : -1;
+                    if (TEAM && (ev[u] & (T - 1)) != mem) ev[u] = -1;
+                }
+#pragma unroll
+                for (int u = 0; u < kClaimBatch; ++u) {
+                    const int t = t0 + u * NT;
+                    const int j = (int)__umulhi((uint32_t)t, m0_magic);
+                    if (t < ncl && t == j * M0) flag[s_pick[j]] |= 1;
+                }
+                uint32_t old[kClaimBatch];
+#pragma unroll
+                for (int u = 0; u < kClaimBatch; ++u)
+                    old[u] = atomicOr(&vis[max(ev[u], 0) >> 5], ev[u] >= 0 ? 1u << (ev[u] & 31) : 0u);
+#pragma unroll
+                for (int u = 0; u < kClaimBatch; ++u)
+                    if (ev[u] >= 0 && !(old[u] & (1u << (ev[u] & 31)))) cid[atomicAdd(&sh.nnew, 1u)] = ev[u];
+            }
         }
         __syncthreads();
         const int nn = (int)sh.nnew;  // this member's share of the new nodes
         n_dist += nn;
-        const int area = (int)(exchanges & 1);
-        uint64_t *xk = T > 1 ? team.keys + (((int64_t)q * 3 + area) * T + mem) * team.slot : nullptr;
+        uint64_t *xk = TEAM ? team_keys() + (int64_t)mem * team.slot : nullptr;
         const uint64_t worst = nbeam == (uint32_t)ef ? beam[nbeam - 1] : 0ull;
         // sharing rows: a new node whose score another query of the group
         // published in this launch is kept or dropped on that score; the
@@ -2365,12 +2456,12 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
             if (gl == 0 && ka > worst) {
                 const uint32_t slot = atomicAdd(&sh.nkeep, 1u);
                 ckey[slot] = ka;
-                if (xk) __hip_atomic_store(xk + slot, ka, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (xk && slot + 1 >= (uint32_t)L) __hip_atomic_store(xk + slot, ka, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             if (gl == 0 && eb >= 0 && kb > worst) {
                 const uint32_t slot = atomicAdd(&sh.nkeep, 1u);
                 ckey[slot] = kb;
-                if (xk) __hip_atomic_store(xk + slot, kb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (xk && slot + 1 >= (uint32_t)L) __hip_atomic_store(xk + slot, kb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
 #pragma unroll
             for (int x = 0; x + 1 < kMultiHeld; x += 2)
@@ -2387,13 +2478,15 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
         if (tid == 0) {
             sh.first = 0xFFFFFFFFu;  // every thread read it before the claim barrier
             sh.ftau = 0u;
+            sh.nx = 0u;
+            sh.nover = 0;
         }
         __syncthreads();
-        if (T > 1) {  // the kept keys of the other members join this member's
-            exchange(area, sh.nkeep, ckey, &sh.nkeep);
+        int nk = (int)sh.nkeep;
+        if constexpr (TEAM) {  // the kept keys of the other members join this member's
+            nk = exchange((uint32_t)nk, (uint32_t)nn, ckey);
             if (sh.team_err) break;
         }
-        int nk = (int)sh.nkeep;
         // A step that keeps many more keys than the beam can take (the first
         // steps of a wide walk, while the beam fills) drops the kept keys that
         // cannot enter it before they are sorted and ranked.  A histogram of
@@ -2615,7 +2708,7 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
         flag2 = tf;
     }
 
-    if (T > 1) {  // the other members' new nodes count as distance evaluations too (one add per wave)
+    if constexpr (TEAM) {  // the other members' new nodes count as distance evaluations too (one add per wave)
         const uint32_t incl = wave_incl_scan(n_other);
         if (lane == kWave - 1) atomicAdd(&sh.nother, incl);
         __syncthreads();
@@ -2636,16 +2729,20 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
         // exact re-rank of the final beam: exact keys into beam2, then by
         // rank; in a team each member scores the entries of its share and
         // the first member gathers all of them
-        if (T == 1) {
+        if constexpr (!TEAM) {
             for (int j = grp; j < nb; j += kGroups) {
                 const int32_t e = key_id(beam[j]);
                 const float sc = row_dot<VEC, BF16, G>(W, e, row_bytes, hs, gl);
                 if (gl == 0) beam2[j] = make_key(sc, e);
             }
         } else {
-            if (tid == 0) sh.nkeep = 0;
+            if (tid == 0) {
+                sh.nkeep = 0;
+                sh.nx = 0u;
+                sh.nover = 0;
+            }
             __syncthreads();
-            uint64_t *xr = team.keys + (((int64_t)q * 3 + 2) * T + mem) * team.slot;
+            uint64_t *xr = team_keys() + (int64_t)mem * team.slot;
             for (int j = grp; j < nb; j += kGroups) {
                 const int32_t e = key_id(beam[j]);
                 if ((e & (T - 1)) != mem) continue;
@@ -2653,11 +2750,12 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
                 if (gl == 0) {
                     const uint32_t slot = atomicAdd(&sh.nkeep, 1u);
                     beam2[slot] = make_key(sc, e);
-                    __hip_atomic_store(xr + slot, make_key(sc, e), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (slot + 1 >= (uint32_t)L)
+                        __hip_atomic_store(xr + slot, make_key(sc, e), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
             __syncthreads();
-            exchange(2, sh.nkeep, beam2, &sh.nkeep);
+            exchange(sh.nkeep, 0u, beam2);
             if (mem != 0) return;
             if (sh.team_err) {
                 for (int t = tid; t < k; t += NT) {
@@ -3143,12 +3241,12 @@ size_t hnsw_multi_lds_bytes(int64_t V, int d, int dtype, int ef_eff, int M0, int
 
 // LDS a search workgroup may take for its dynamic carve-up: the device's
 // per-block limit less a reserve for the kernels' static variables (2.2 KB
-// in hnsw_multi_kernel: shared counters, picks, cache ids and the offsets of
+// in hnsw_multi_kernel: shared counters, picks, cache ids and the places of
 // up to kMaxTeam members' keys).
 size_t hnsw_lds_limit()
 {
     constexpr int kStaticReserve = 3072;
-    static_assert((kMaxTeam + 1) * 4 + 1280 <= kStaticReserve, "team offsets fit the static reserve");
+    static_assert(kMaxTeam * 4 + 1280 <= kStaticReserve, "team offsets fit the static reserve");
     int dev = 0, v = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 64 * 1024 - kStaticReserve;
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess || v <= kStaticReserve)
@@ -3157,10 +3255,12 @@ size_t hnsw_lds_limit()
 }
 
 namespace {
-__global__ void team_clear_kernel(uint64_t *__restrict__ tags, int n)
+// Zeroes the lines of every query (blockIdx.y): n words, `stride` words from
+// one query's to the next's.
+__global__ void team_clear_kernel(uint64_t *__restrict__ lines, int64_t stride, int n)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) tags[i] = 0ull;
+    if (i < n) lines[blockIdx.y * stride + i] = 0ull;
 }
 
 // Keys a member passes at one exchange: the most new nodes of a step, or a
@@ -3169,17 +3269,16 @@ int team_slot(const HnswLaunch &a) { return std::max(a.width * a.M0, a.ef_eff); 
 
 size_t round256(size_t n) { return (n + 255) & ~(size_t)255; }
 
-// The team workspace: keys [B][3][team][slot] u64, then the published
-// counts [B][3][team] u64, each 256-byte aligned.
-TeamArgs team_layout(void *ws, int B, int team, int slot)
+// The team workspace: u64 words, [B][3][team][slot]; of a query, the keys of
+// both sets, then (in the third part) the lines of both.
+TeamArgs team_layout(void *ws, int team, int slot)
 {
-    char *p = static_cast<char *>(ws);
     TeamArgs t;
     t.size = team;
     t.slot = slot;
-    t.keys = reinterpret_cast<uint64_t *>(p);
-    p += round256((size_t)B * 3 * team * slot * 8);
-    t.tags = reinterpret_cast<uint64_t *>(p);
+    t.line = 1;
+    while (2 * t.line * team <= kTeamWords && 4 * t.line <= slot) t.line *= 2;
+    t.keys = static_cast<uint64_t *>(ws);
     return t;
 }
 }  // namespace
@@ -3187,8 +3286,7 @@ TeamArgs team_layout(void *ws, int B, int team, int slot)
 size_t hnsw_team_workspace_bytes(const HnswLaunch &a)
 {
     if (a.team <= 1) return 0;
-    const int slot = team_slot(a);
-    return round256((size_t)a.B * 3 * a.team * slot * 8) + round256((size_t)a.B * 3 * a.team * 8);
+    return round256((size_t)a.B * 3 * a.team * team_slot(a) * 8);
 }
 
 namespace {
@@ -3292,16 +3390,18 @@ template <int NT, int VEC, bool BF16, int G>
 hipError_t hnsw_launch(const HnswLaunch &a, size_t lds, hipStream_t s)
 {
     if (a.width > 1 || a.q8 || a.team > 1 || a.share > 1) {
-        auto kern = a.share > 1 ? (a.q8 ? hnsw_multi_kernel<NT, VEC, BF16, G, true, true>
-                                        : hnsw_multi_kernel<NT, VEC, BF16, G, false, true>)
-                                : (a.q8 ? hnsw_multi_kernel<NT, VEC, BF16, G, true, false>
-                                        : hnsw_multi_kernel<NT, VEC, BF16, G, false, false>);
+        auto kern = a.share > 1  ? (a.q8 ? hnsw_multi_kernel<NT, VEC, BF16, G, true, Form::kShare>
+                                         : hnsw_multi_kernel<NT, VEC, BF16, G, false, Form::kShare>)
+                    : a.team > 1 ? (a.q8 ? hnsw_multi_kernel<NT, VEC, BF16, G, true, Form::kTeam>
+                                         : hnsw_multi_kernel<NT, VEC, BF16, G, false, Form::kTeam>)
+                                 : (a.q8 ? hnsw_multi_kernel<NT, VEC, BF16, G, true, Form::kOne>
+                                         : hnsw_multi_kernel<NT, VEC, BF16, G, false, Form::kOne>);
         if (lds > 64 * 1024) {
             hipError_t e =
                 hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
         }
-        TeamArgs team{1, 0, nullptr, nullptr};
+        TeamArgs team{1, 0, 1, nullptr};
         if (a.team > 1) {
             // every member of every query must be resident at once
             int per = 0, dev = 0, cus = 0;
@@ -3310,9 +3410,10 @@ hipError_t hnsw_launch(const HnswLaunch &a, size_t lds, hipStream_t s)
             if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
             if (e != hipSuccess) return e;
             if ((int64_t)per * cus < (int64_t)a.B * a.team) return hipErrorCooperativeLaunchTooLarge;
-            team = team_layout(a.team_ws, a.B, a.team, team_slot(a));
-            const int ntag = a.B * 3 * a.team;
-            team_clear_kernel<<<(ntag + 255) / 256, 256, 0, s>>>(team.tags, ntag);
+            team = team_layout(a.team_ws, a.team, team_slot(a));
+            const int64_t area = (int64_t)a.team * team.slot;
+            const int words = 2 * a.team * team.line;
+            team_clear_kernel<<<dim3((words + 255) / 256, a.B), 256, 0, s>>>(team.keys + 2 * area, 3 * area, words);
             e = hipGetLastError();
             if (e != hipSuccess) return e;
         }

@@ -389,6 +389,37 @@ def test_hnsw_team_equals_one_workgroup(vie, team):
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
 
 
+@pytest.mark.parametrize("M,M0,width,k,ef,team", [
+    (2, 2, 1, 1, 1, 8),        # a line of one word: a header and no key
+    (3, 6, 1, 1, 1, 256),      # one key a line; lists that are no whole quads
+    (5, 10, 7, 10, 30, 64),    # ragged lists and steps
+    (8, 16, 128, 50, 300, 2),  # long lines
+    (8, 16, 128, 50, 300, 256),  # 7 keys a line
+    (4, 12, 5, 10, 200, 16),   # quads that a step does not fill
+])
+def test_hnsw_team_lines(vie, M, M0, width, k, ef, team):
+    """The lines of a team's exchange at their smallest and longest, and lists
+    with and without whole quads: bitwise the search of one workgroup, over
+    launches that reuse one workspace."""
+    V, d = 1500, 64
+    W = synth.make_w(V, d, synth.BF16, 1890 + M0)
+    H, _ = synth.make_queries(W, synth.BF16, max(1, min(5, 256 // team)), 1891)
+    g = O.hnsw_build(W, synth.BF16, M, 40, 5, M0=M0)
+    with tempfile.TemporaryDirectory() as tmp:
+        ix = _load_on_gpu(vie, g, W, synth.BF16, tmp)
+    h = dev_tensor(vie, H, synth.BF16)
+    ix.attach_int8(*vie.quantize_rows(ix._W_dev, synth.BF16))
+    for int8 in (False, True):
+        say("team lines", M0, width, ef, team, int8)
+        one = ix.query(h, k, ef, stats=True, width=width, int8=int8, trace_cap=ef + 1024)
+        for _ in range(3):
+            many = ix.query(h, k, ef, stats=True, width=width, int8=int8, trace_cap=ef + 1024, team=team)
+            torch.cuda.synchronize()
+            for a, b, name in zip(one, many, ("ids", "logits", "stats", "trace")):
+                a, b = a.cpu().numpy(), b.cpu().numpy()
+                assert np.array_equal(a.view(np.uint32), b.view(np.uint32)), name
+
+
 @pytest.mark.parametrize("dtype,d", [(synth.BF16, 96), (synth.F32, 64)])
 def test_hnsw_row_sharing_equals_independent(vie, dtype, d):
     """Queries that share fetched rows in groups (a row fetched for one query
