@@ -2339,11 +2339,13 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
                     }
             }
         } else {
-            for (int t0 = tid; t0 < ncl; t0 += kClaimBatch * NT) {
-                int32_t ev[kClaimBatch];
+            // N entries a thread, NT apart, from entry b0 on
+            auto claim_some = [&](auto count, int b0) {
+                constexpr int N = decltype(count)::value;
+                int32_t ev[N];
 #pragma unroll
-                for (int u = 0; u < kClaimBatch; ++u) {
-                    const int t = min(t0 + u * NT, ncl - 1);
+                for (int u = 0; u < N; ++u) {
+                    const int tu = b0 + u * NT + tid, t = min(tu, ncl - 1);
                     const int j = (int)__umulhi((uint32_t)t, m0_magic), slot = t - j * M0;
                     const int pj = s_pick[j];
                     const int32_t c = key_id(beam[pj]);
@@ -2353,23 +2355,34 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
                     // would be a generic load, which waits on both memory counters)
                     const int32_t ec = src >= 0 ? lcache[max(src, 0) * M0 + slot] : -1;
                     const int32_t eg = src < 0 ? adj0[(int64_t)c * M0 + slot] : -1;
-                    ev[u] = t0 + u * NT < ncl ? (src >= 0 ? ec : eg) : -1;
+                    ev[u] = tu < ncl ? (src >= 0 ? ec : eg) : -1;
                     if (TEAM && (ev[u] & (T - 1)) != mem) ev[u] = -1;
                 }
 #pragma unroll
-                for (int u = 0; u < kClaimBatch; ++u) {
-                    const int t = t0 + u * NT;
+                for (int u = 0; u < N; ++u) {
+                    const int t = b0 + u * NT + tid;
                     const int j = (int)__umulhi((uint32_t)t, m0_magic);
                     if (t < ncl && t == j * M0) flag[s_pick[j]] |= 1;
                 }
-                uint32_t old[kClaimBatch];
+                uint32_t old[N];
 #pragma unroll
-                for (int u = 0; u < kClaimBatch; ++u)
-                    old[u] = atomicOr(&vis[max(ev[u], 0) >> 5], ev[u] >= 0 ? 1u << (ev[u] & 31) : 0u);
+                for (int u = 0; u < N; ++u) {
+                    old[u] = ~0u;
+                    if (ev[u] >= 0) old[u] = atomicOr(&vis[ev[u] >> 5], 1u << (ev[u] & 31));
+                }
 #pragma unroll
-                for (int u = 0; u < kClaimBatch; ++u)
-                    if (ev[u] >= 0 && !(old[u] & (1u << (ev[u] & 31)))) cid[atomicAdd(&sh.nnew, 1u)] = ev[u];
-            }
+                for (int u = 0; u < N; ++u)
+                    if (!(old[u] & (1u << (ev[u] & 31)))) cid[atomicAdd(&sh.nnew, 1u)] = ev[u];
+            };
+            // As many entries as the rest holds, and no claim without an entry:
+            // claims of nothing meet on one word of the bitmap and are served
+            // one by one.  One query on one workgroup, int8 rows: 95668 x 656
+            // at 8 per step, ef 685, 1423 -> 1277 us; 9488 x 704 (bf16 rows) at
+            // 32 per step, ef 372, 266 -> 236 us.
+            int b0 = 0;
+            for (; ncl - b0 > 2 * NT; b0 += kClaimBatch * NT) claim_some(std::integral_constant<int, kClaimBatch>(), b0);
+            if (ncl - b0 > NT) claim_some(std::integral_constant<int, 2>(), b0);
+            else if (ncl > b0) claim_some(std::integral_constant<int, 1>(), b0);
         }
         __syncthreads();
         const int nn = (int)sh.nnew;  // this member's share of the new nodes
