@@ -3299,7 +3299,8 @@ TeamArgs team_layout(void *ws, int team, int slot)
 size_t hnsw_team_workspace_bytes(const HnswLaunch &a)
 {
     if (a.team <= 1) return 0;
-    return round256((size_t)a.B * 3 * a.team * team_slot(a) * 8);
+    // (the last part, three words a member, is spare: callers know this size)
+    return round256((size_t)a.B * 3 * a.team * team_slot(a) * 8) + round256((size_t)a.B * 3 * a.team * 8);
 }
 
 namespace {
