@@ -678,6 +678,11 @@ __global__ __launch_bounds__(kMergeThreads) void dense_merge_kernel(const float 
         key[3] = ((uint64_t)v1.w << 32) | v1.z;
     }
     const uint64_t m = key[0];  // the slab's maximum
+    // keys of each list that T is taken from: with fewer than two slabs for
+    // each wanted key the maxima alone give a T far below the k-th largest
+    // key (none at all with fewer slabs than k), the whole lists one close to
+    // it.  (The k-th largest of any keys is a lower bound of it.)
+    const int nl = nwg < 2 * k ? kTopR : 1;
     if (tid == 0) {
         s_nc = 0;
         s_n = 0;
@@ -688,8 +693,8 @@ __global__ __launch_bounds__(kMergeThreads) void dense_merge_kernel(const float 
         s_bucket = kMergeBuckets;
     }
     if (tid < kMergeBuckets) hist[tid] = 0u;
-    // 1. T, a lower bound of the k-th largest slab maximum.  First one pass:
-    //    a histogram of the maxima by their distance below the largest one
+    // 1. T, a lower bound of the k-th largest of those keys.  First one pass:
+    //    a histogram of them by their distance below the largest one
     //    in the order space of the logits, 2^kMergeBucketShift per bucket
     //    (1/32 of a binade for positive logits); T is the lower edge of the
     //    bucket in which the count from the top reaches k.  The slabs above
@@ -710,8 +715,11 @@ __global__ __launch_bounds__(kMergeThreads) void dense_merge_kernel(const float 
         uint32_t top = s_wmax[0];
 #pragma unroll
         for (int x = 1; x < kMergeWaves; ++x) top = max(top, s_wmax[x]);
-        const uint32_t dist = (top - mo) >> kMergeBucketShift;
-        if (tid < nwg && dist < (uint32_t)kMergeBuckets) atomicAdd(&hist[dist], 1u);
+#pragma unroll
+        for (int i = 0; i < kTopR; ++i) {
+            const uint32_t dist = (top - (uint32_t)(key[i] >> 32)) >> kMergeBucketShift;
+            if (i < nl && key[i] != 0ull && dist < (uint32_t)kMergeBuckets) atomicAdd(&hist[dist], 1u);
+        }
         __syncthreads();
         if (tid < kWave) {  // wave 0: the bucket where the count from the top reaches k
             constexpr int per = kMergeBuckets / kWave;
@@ -753,12 +761,19 @@ __global__ __launch_bounds__(kMergeThreads) void dense_merge_kernel(const float 
         }
         const uint64_t t = __shfl(srt, k - 1, kWave);
         if (tid == 0) s_T = t;
-    } else if (nwg >= k) {
-        // 1'. any k: T by radix select over the maxima, 8 bits per pass from
+    } else if (nl * nwg >= k) {
+        // 1'. any k: T by radix select over the keys, 8 bits per pass from
         //     the first bit where they differ, until the bucket of the k-th
-        //     largest is taken whole (so exactly k slabs have maximum >= T)
+        //     largest is taken whole (so exactly k keys are >= T; T = 0 if
+        //     the lists hold fewer)
         __syncthreads();
-        uint64_t a = tid < nwg ? m : ~0ull, o = m;
+        uint64_t a = ~0ull, o = 0ull;
+#pragma unroll
+        for (int i = 0; i < kTopR; ++i)
+            if (i < nl && tid < nwg) {
+                a &= key[i];
+                o |= key[i];
+            }
 #pragma unroll
         for (int x = 32; x >= 1; x >>= 1) {
             a &= __shfl_xor(a, x, kWave);
@@ -782,7 +797,9 @@ __global__ __launch_bounds__(kMergeThreads) void dense_merge_kernel(const float 
                 const uint64_t dmask = (1ull << (hi - lo)) - 1ull;
                 if (tid < 256) hist[tid] = 0u;
                 __syncthreads();
-                if (tid < nwg && (m & known) == prefix) atomicAdd(&hist[(m >> lo) & dmask], 1u);
+#pragma unroll
+                for (int i = 0; i < kTopR; ++i)
+                    if (i < nl && tid < nwg && (key[i] & known) == prefix) atomicAdd(&hist[(key[i] >> lo) & dmask], 1u);
                 __syncthreads();
                 if (tid < kWave) {  // wave 0: the bucket holding the want-th largest
                     uint32_t c[4], sum = 0;
@@ -812,7 +829,7 @@ __global__ __launch_bounds__(kMergeThreads) void dense_merge_kernel(const float 
         }
         if (tid == 0) s_T = prefix;
     }
-    // (fewer slabs than k: T = 0, every slab qualifies)
+    // (lists of fewer than k keys: T = 0, every slab qualifies)
     __syncthreads();
     {
         // 2. every key >= T lies in a slab whose maximum is >= T.  A slab

@@ -5,6 +5,7 @@ k = V, B above one pass, odd row widths, zero queries and ef >= |V|."""
 import os
 import sys
 import tempfile
+import time
 
 import numpy as np
 import pytest
@@ -87,11 +88,14 @@ DENSE_CASES = [
     (1200, 6144, synth.BF16, 1, 50),   # bf16, 12 of 12 chunks per lane
     (1500, 3328, synth.F32, 1, 10),    # 13 chunks per lane: the slab kernel
     (4000, 256, synth.F32, 2, 40),     # fp32, two queries, one chunk per lane
-    # fewer slabs than k over more rows than the merge holds in LDS: every
-    # row is a candidate and the merge bisects the whole key space
-    (5000, 64, synth.BF16, 4, 50),     # matrix cores: 40 slabs of 128 rows
+    (5000, 64, synth.BF16, 4, 50),     # matrix cores: 250 slabs of 20 rows
+    # fewer slabs than k: the merge's bound comes from the slabs' lists
     (5000, 64, synth.F32, 1, 1024),    # vector path: 1000 slabs of 5 rows
     (151936, 64, synth.BF16, 1, 1024), # vector path: 1020 slabs of 149 rows
+    # lists of fewer than k keys over more rows than the merge holds in LDS:
+    # every row is a candidate and the merge bisects the whole key space
+    (5000, 64, synth.BF16, 4, 1024),   # matrix cores: 250 slabs of 20 rows
+    (5000, 64, synth.F32, 4, 1024),
 ]
 
 
@@ -123,6 +127,12 @@ def test_dense_topk_matches_oracle(vie, V, d, dtype, B, k):
     (70001, 136, synth.BF16, 7, 100),  # two row tiles, a ragged last block, scalar logit stores
     (300, 516, synth.F32, 64, 100),    # a few rows per workgroup
     (5, 4, synth.F32, 3, 5),           # one 16-byte piece per row, two workgroups
+    # fewer than two slabs for each wanted key
+    (32768, 36, synth.F32, 3, 300),    # 256 slabs
+    (50257, 40, synth.BF16, 5, 400),
+    (66000, 24, synth.F32, 5, 1024),   # several slabs per workgroup
+    (9001, 64, synth.BF16, 9, 900),    # most of the listed keys
+    (300, 516, synth.F32, 3, 300),     # k = V: every listed key
 ])
 def test_dense_batches_on_the_matrix_cores(vie, V, d, dtype, B, k):
     say("dense batch", V, d, dtype, B, k)
@@ -151,12 +161,34 @@ def test_dense_batch_keeps_nonfinite_values_in_their_rows(vie, dtype):
     assert (ids[:, 0] == 1234).all() and torch.isinf(lg[:, 0]).all() and torch.isfinite(lg[:, 1:]).all()
 
 
-@pytest.mark.parametrize("B,k", [(1, 50), (1, 100), (16, 50), (16, 100)])
+@pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
+def test_dense_batch_time_does_not_jump_with_k(vie, dtype):
+    # 256 slabs or fewer: with more wanted keys than slabs the merge once had
+    # no bound and read every logit 64 times (20 times the call's time at
+    # k = 128); a bound from the slabs' lists costs a few us more
+    V, d, B = 32768, 64, 4
+    W = dev_tensor(vie, synth.make_w(V, d, dtype, 51), dtype)
+    h = dev_tensor(vie, synth.make_queries(synth.make_w(V, d, dtype, 51), dtype, B, 52)[0], dtype)
+    head = vie.DenseHead(W, max_batch=B, max_k=512)
+    took = {}
+    for k in (128, 300, 128, 300):
+        head(h, k)
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        for _ in range(50):
+            head(h, k)
+        torch.cuda.synchronize()
+        took[k] = min(took.get(k, 1.0), time.perf_counter() - t)
+    assert took[300] < 4 * took[128], took
+
+
+@pytest.mark.parametrize("B,k", [(1, 50), (1, 100), (16, 50), (16, 100), (16, 300), (1, 700)])
 def test_dense_far_maximum_takes_the_exact_fallbacks(vie, B, k):
     # one planted row per query scores about 2^20 times the usual maximum, so
     # the merge's histogram window (eight binades below the largest slab
     # maximum) holds fewer than k slab maxima: k <= 64 takes the sorting
-    # network over the maxima, larger k the radix select
+    # network over the maxima, larger k the radix select (over the slabs'
+    # whole lists where there are fewer than two slabs for each wanted key)
     V, d = 20000, 128
     W = synth.make_w(V, d, synth.BF16, 141)
     H, _ = synth.make_queries(W, synth.BF16, B, 142)
