@@ -4,9 +4,9 @@
 //                        retrieved ids.
 //   dense_stream_kernel, exact head z = W_out h fused with top-k (Section 3;
 //   dense_slab_kernel,   the dense baseline of Section 4.1): slab logits on
-//   dense_tile_kernel,   the vector ALUs (one to a few queries) or the
-//   dense_merge_kernel   matrix cores (batches), then the top k from the
-//                        slabs' candidate lists.
+//   dense_mfma_kernel,   the vector ALUs (one to a few queries) or the
+//   dense_tile_kernel,   matrix cores (batches), then the top k from the
+//   dense_merge_kernel   slabs' candidate lists.
 //   hnsw_kernel          HNSW k-NN search (Sections 2-3; Malkov & Yashunin
 //                        Algorithms 2 and 5), one workgroup per query.
 //   hnsw_multi_kernel    the same search expanding up to 128 beam entries
@@ -607,12 +607,29 @@ __device__ __forceinline__ uint64_t lane_reverse(uint64_t v, int lane)
     return ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(v >> 32), src) << 32) | (uint32_t)__shfl((int)(uint32_t)v, src);
 }
 
-// Adds the keys >= T of rows [row0, row0 + nrows) (clamped to V) of zq to
-// gat; the whole workgroup takes part, kGatherBatch loads in flight per
-// thread.  Element i is row i % rows_per of listed slab i / rows_per.
+// Where the rows of a slab lie: in `blks` blocks of `blk_rows` rows each.
+// With step 1 a slab's blocks follow each other (slab s has rows s * blks *
+// blk_rows and on); else they lie `step` blocks apart, and each run of
+// blks * step blocks holds the slabs of `step` workgroups.
+struct SlabRows {
+    int blks, blk_rows, step;
+    __host__ __device__ int rows() const { return blks * blk_rows; }
+    // row i of slab s
+    __device__ __forceinline__ int64_t at(int s, int i) const
+    {
+        if (step == 1) return (int64_t)s * rows() + i;
+        const int t = i / blk_rows, run = s / step;
+        return (int64_t)((run * blks + t) * step + (s - run * step)) * blk_rows + (i - t * blk_rows);
+    }
+};
+
+// Adds the keys >= T of the listed slabs' rows (those below V) of zq to gat;
+// the whole workgroup takes part, kGatherBatch loads in flight per thread.
+// Element i is row i % rows_per of listed slab i / rows_per.
 __device__ __forceinline__ void gather_slabs(const float *__restrict__ zq, int64_t V, const int *slabs, int nslab,
-                                             int rows_per, uint64_t T, uint64_t *gat, uint32_t *s_n)
+                                             SlabRows sr, uint64_t T, uint64_t *gat, uint32_t *s_n)
 {
+    const int rows_per = sr.rows();
     const int tid = threadIdx.x;
     const int total = nslab * rows_per;
     const int step_c = kMergeThreads / rows_per, step_r = kMergeThreads % rows_per;
@@ -625,7 +642,7 @@ __device__ __forceinline__ void gather_slabs(const float *__restrict__ zq, int64
             row[j] = -1;
             z[j] = 0.0f;
             if (c < nslab) {
-                const int64_t r = (int64_t)slabs[c] * rows_per + rr;
+                const int64_t r = sr.at(slabs[c], rr);
                 if (r < V) {
                     row[j] = r;
                     z[j] = zq[r];
@@ -653,7 +670,7 @@ __device__ __forceinline__ void gather_slabs(const float *__restrict__ zq, int64
 
 __global__ __launch_bounds__(kMergeThreads) void dense_merge_kernel(const float *__restrict__ zbuf,
                                                                      const uint64_t *__restrict__ tops, int64_t V,
-                                                                     int rows_per_wg, int nwg, int k,
+                                                                     SlabRows sr, int nwg, int k,
                                                                      int32_t *__restrict__ ids,
                                                                      float *__restrict__ logits)
 {
@@ -850,7 +867,7 @@ __global__ __launch_bounds__(kMergeThreads) void dense_merge_kernel(const float 
             }
         }
         __syncthreads();
-        if (s_nscan) gather_slabs(zq, V, scan, (int)s_nscan, rows_per_wg, T, gat, &s_n);
+        if (s_nscan) gather_slabs(zq, V, scan, (int)s_nscan, sr, T, gat, &s_n);
     }
     __syncthreads();
     const uint64_t T = s_T;
@@ -885,6 +902,7 @@ __global__ __launch_bounds__(kMergeThreads) void dense_merge_kernel(const float 
     //      the candidate slabs by bisection on the key, then order by rank
     //      among the ones above it (a slow path for degenerate inputs only).
     __shared__ unsigned long long s_cnt;
+    const int rows_per = sr.rows();
     uint64_t lo = T, hi = ~0ull;  // invariant: count(>= lo) >= k, count(>= hi + 1) < k
     while (lo < hi) {
         // lo < mid <= hi, so every round shrinks [lo, hi]; written so that
@@ -893,9 +911,9 @@ __global__ __launch_bounds__(kMergeThreads) void dense_merge_kernel(const float 
         if (tid == 0) s_cnt = 0;
         __syncthreads();
         unsigned long long c = 0;
-        for (int i = tid; i < nc * rows_per_wg; i += kMergeThreads) {
-            const int cc = i / rows_per_wg;
-            const int64_t row = (int64_t)cand[cc] * rows_per_wg + (i - cc * rows_per_wg);
+        for (int i = tid; i < nc * rows_per; i += kMergeThreads) {
+            const int cc = i / rows_per;
+            const int64_t row = sr.at(cand[cc], i - cc * rows_per);
             if (row < V && make_key(zq[row], (int32_t)row) >= mid) ++c;
         }
         atomicAdd(&s_cnt, c);
@@ -905,9 +923,9 @@ __global__ __launch_bounds__(kMergeThreads) void dense_merge_kernel(const float 
     }
     if (tid == 0) s_n = 0;
     __syncthreads();
-    for (int i = tid; i < nc * rows_per_wg; i += kMergeThreads) {
-        const int c = i / rows_per_wg;
-        const int64_t row = (int64_t)cand[c] * rows_per_wg + (i - c * rows_per_wg);
+    for (int i = tid; i < nc * rows_per; i += kMergeThreads) {
+        const int c = i / rows_per;
+        const int64_t row = sr.at(cand[c], i - c * rows_per);
         if (row < V) {
             const uint64_t key = make_key(zq[row], (int32_t)row);
             if (key >= lo) {
@@ -928,7 +946,273 @@ __global__ __launch_bounds__(kMergeThreads) void dense_merge_kernel(const float 
 }
 
 // ---------------------------------------------------------------------------
-// dense head, batches: skinny GEMM on the matrix cores
+// dense head, batched bf16: skinny GEMM on the matrix cores, register-staged
+// ---------------------------------------------------------------------------
+//
+// For several queries at once the slab logits come from
+// v_mfma_f32_16x16x32_bf16 (16 rows of W_out times 16 queries per
+// instruction, fp32 accumulation).  Workgroup w owns a slab of rows; each of
+// its four waves takes 32 rows at a time against all the queries of the pass
+// (NQT 16-query tiles) and walks the row width in stages of KC columns.
+//
+// The operand layout of the instruction wants 16 different rows per load,
+// which scatters a wave's accesses over 16 rows (64 bytes of each); loaded
+// that way straight into the operand registers, a 128256 x 3072 bf16 W_out
+// streamed at 3.7-4.8 TB/s per call on MI355X (64 to 4 queries), against
+// 5.0-6.1 TB/s staged.  So each wave stages its rows through its own slice of
+// LDS: a stage is read with non-temporal loads that cover whole contiguous
+// row segments (the next one or two stages are loaded while the current one
+// is multiplied), written to LDS and read back in operand layout: lane
+// (r, g) = (lane % 16, lane / 16) takes columns 32 t + 8 g .. + 7 of step t
+// for its row r and the same columns of its query.  The queries' columns of
+// a stage are staged in LDS once for the four waves (read with the row
+// stage, one stage ahead), which keeps the registers for loads in flight.
+// The slab's logits (16-byte stores) and its kTopR largest keys per query go
+// to the workspace in the layout of the single-query path, and
+// dense_merge_kernel selects the top k.  dense_tile_kernel below takes the
+// batches that it serves faster (bf16_tiles states which).
+//
+// Staged rows are padded by 32 bytes.  A 16-byte LDS read of 64 lanes takes
+// four cycles on gfx950 when no bank is over-used; measured with the LDS
+// counters, the operand read (16 rows, four 16-byte pieces each) takes four
+// cycles when the row pitch is 32 bytes more than a multiple of 64 and eight
+// cycles (half of them bank conflicts) when it is 16 or 48 more, while the
+// stage writes take eight cycles at any of these pitches.
+
+#ifndef VIE_MFMA_MAX_WGS
+#define VIE_MFMA_MAX_WGS 1024
+#endif
+// Stage width (columns) and W stages loaded ahead, per pass size (up to
+// 16, 32 or 64 queries); defaults measured on MI355X.
+#ifndef VIE_MFMA_KC1
+#define VIE_MFMA_KC1 256
+#endif
+#ifndef VIE_MFMA_LA1
+#define VIE_MFMA_LA1 1
+#endif
+#ifndef VIE_MFMA_KC2
+#define VIE_MFMA_KC2 128
+#endif
+#ifndef VIE_MFMA_LA2
+#define VIE_MFMA_LA2 2
+#endif
+#ifndef VIE_MFMA_KC4
+#define VIE_MFMA_KC4 128
+#endif
+#ifndef VIE_MFMA_LA4
+#define VIE_MFMA_LA4 1
+#endif
+
+constexpr int kMfmaWaves = 4;
+constexpr int kMfmaThreads = kMfmaWaves * kWave;
+constexpr int kBatchMaxNB = 64;                   // queries per pass of either batch kernel
+constexpr int kBatchMinB = 3;
+constexpr int kMfmaMaxWgs = VIE_MFMA_MAX_WGS;
+constexpr int kMfmaRowsPerWave = 32;              // two 16-row tiles
+constexpr int kMfmaRowsPerIter = kMfmaWaves * kMfmaRowsPerWave;
+static_assert(kMfmaMaxWgs <= kMergeThreads, "the merge gives every slab maximum a thread");
+
+#ifndef VIE_MFMA_PAD
+#define VIE_MFMA_PAD 32
+#endif
+constexpr int mfma_pitch(int KC) { return KC * 2 + VIE_MFMA_PAD; }  // LDS bytes per staged row (padded)
+constexpr size_t mfma_lds(int NQT, int KC)
+{
+    return (size_t)(kMfmaWaves * kMfmaRowsPerWave + 16 * NQT) * mfma_pitch(KC);
+}
+
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
+                                                   c, 0, 0, 0);
+}
+
+template <int NQT, int KC, int LA>
+__global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(2))) void dense_mfma_kernel(const uint16_t *__restrict__ W, int64_t V, int d,
+                                                                   const uint16_t *__restrict__ hq, int nq,
+                                                                   int rows_per_wg, float *__restrict__ zout,
+                                                                   uint64_t *__restrict__ tops)
+{
+    extern __shared__ __align__(16) char smem[];
+    __shared__ uint64_t s_top[16 * NQT][kMfmaWaves][kTopR];
+    constexpr int kPitch = mfma_pitch(KC);
+    constexpr int kSteps = KC / 32;                     // MFMA steps per stage
+    constexpr int kLanesPerRow = KC / 8;                // 16-byte pieces per staged row
+    constexpr int kRowsPerLoad = kWave / kLanesPerRow;
+    constexpr int kLoads = kMfmaRowsPerWave / kRowsPerLoad;  // W stage loads per lane
+    constexpr int kHLoads = 16 * NQT * kLanesPerRow / kMfmaThreads;  // query stage loads per thread
+    static_assert(kRowsPerLoad >= 1 && kMfmaRowsPerWave % kRowsPerLoad == 0, "stage shape");
+    static_assert(kHLoads >= 1 && (16 * NQT * kLanesPerRow) % kMfmaThreads == 0, "query stage shape");
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int r = lane & 15, g = lane >> 4;
+    char *slice = smem + (size_t)wave * kMfmaRowsPerWave * kPitch;
+    char *hsl = smem + (size_t)kMfmaWaves * kMfmaRowsPerWave * kPitch;  // [16 NQT][kPitch]
+    const int64_t r0 = (int64_t)blockIdx.x * rows_per_wg;
+    const int nrows = (int)max<int64_t>(0, min<int64_t>(rows_per_wg, V - r0));
+    const int nstage = (d + KC - 1) / KC;
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    // slab starts are multiples of 128 rows, so with V % 4 == 0 every group
+    // of four rows of a query's logits is 16-byte aligned
+    const bool zvec = (V & 3) == 0 && ((uintptr_t)zout & 15) == 0;
+    // W staging: load j of a lane covers row kRowsPerLoad j + srow, 16 bytes
+    // at column scol of the stage
+    const int srow = lane / kLanesPerRow, scol = 8 * (lane % kLanesPerRow);
+
+    // query staging: load j of a thread covers query row L / kLanesPerRow
+    // (padding rows repeat the last query), column hcol[j]
+    const uint16_t *hrowp[kHLoads];
+    int hoff[kHLoads], hcol[kHLoads];
+#pragma unroll
+    for (int j = 0; j < kHLoads; ++j) {
+        const int L = j * kMfmaThreads + tid;
+        const int row = L / kLanesPerRow;
+        hcol[j] = 8 * (L % kLanesPerRow);
+        hrowp[j] = hq + (int64_t)min(row, nq - 1) * d;
+        hoff[j] = row * kPitch + hcol[j] * 2;
+    }
+
+    uint64_t best[NQT][kTopR];
+#pragma unroll
+    for (int n = 0; n < NQT; ++n)
+#pragma unroll
+        for (int i = 0; i < kTopR; ++i) best[n][i] = 0ull;
+
+    // Every wave runs the same number of iterations (the workgroup barriers
+    // need it); rows past the slab are clamped and discarded.  W stages run
+    // LA ahead: stage st's loads sit in buffer st % LA (the loop is unrolled
+    // over the buffers, so no in-flight load is ever copied); the query stage
+    // runs one ahead.  Every stage issues the same loads with no branch
+    // around them, in the order they are consumed (columns past the row are
+    // clamped to its last piece and replaced by zeros when staged; the loads
+    // of stages past the end re-read a query piece, which stays in L2), with
+    // scheduling barriers keeping that order: the compiler then counts the
+    // loads in flight exactly and waits only for the stage being staged, not
+    // for the ones still ahead.
+    for (int rb0 = 0; rb0 < nrows; rb0 += kMfmaRowsPerIter) {
+        const int rb = rb0 + wave * kMfmaRowsPerWave;
+        const uint16_t *wrow[kLoads];
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j)
+            wrow[j] = W + (r0 + min(rb + kRowsPerLoad * j + srow, nrows - 1)) * (int64_t)d;
+        u32x4 pre[LA][kLoads];
+        u32x4 hpre[kHLoads];
+#pragma unroll
+        for (int b = 0; b < LA; ++b) {
+#pragma unroll
+            for (int j = 0; j < kLoads; ++j)
+                pre[b][j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(
+                    b < nstage ? wrow[j] + min(b * KC + scol, d - 8) : hrowp[0]));
+            __builtin_amdgcn_sched_barrier(0);  // keep the issue order
+            if (b == 0) {
+#pragma unroll
+                for (int j = 0; j < kHLoads; ++j)
+                    hpre[j] = *reinterpret_cast<const u32x4 *>(hrowp[j] + min(hcol[j], d - 8));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        f32x4 acc[2][NQT];
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int n = 0; n < NQT; ++n) acc[m][n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+        for (int st0 = 0; st0 < nstage; st0 += LA) {
+#pragma unroll
+            for (int b = 0; b < LA; ++b) {
+                const int st = st0 + b;
+                if (st >= nstage) break;  // uniform across the workgroup
+                const int c0 = st * KC;
+                __syncthreads();  // every wave is done with the previous query stage
+                // this stage into LDS, then the loads of stage st + 1 (queries)
+                // and st + LA (W)
+                const bool win = c0 + scol + 8 <= d;
+#pragma unroll
+                for (int j = 0; j < kLoads; ++j)
+                    *reinterpret_cast<u32x4 *>(slice + (kRowsPerLoad * j + srow) * kPitch + scol * 2) =
+                        win ? pre[b][j] : zero;
+#pragma unroll
+                for (int j = 0; j < kHLoads; ++j)
+                    *reinterpret_cast<u32x4 *>(hsl + hoff[j]) = c0 + hcol[j] + 8 <= d ? hpre[j] : zero;
+#pragma unroll
+                for (int j = 0; j < kHLoads; ++j)
+                    hpre[j] = *reinterpret_cast<const u32x4 *>(hrowp[j] + min(c0 + KC + hcol[j], d - 8));
+                __builtin_amdgcn_sched_barrier(0);
+                const bool ahead = st + LA < nstage;
+#pragma unroll
+                for (int j = 0; j < kLoads; ++j)
+                    pre[b][j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(
+                        ahead ? wrow[j] + min(c0 + LA * KC + scol, d - 8) : hrowp[0]));
+                __syncthreads();  // the query stage is complete
+#pragma unroll
+                for (int t = 0; t < kSteps; ++t) {
+                    u32x4 a[2];
+#pragma unroll
+                    for (int m = 0; m < 2; ++m)
+                        a[m] = *reinterpret_cast<const u32x4 *>(slice + (m * 16 + r) * kPitch + (32 * t + 8 * g) * 2);
+#pragma unroll
+                    for (int n = 0; n < NQT; ++n) {
+                        const u32x4 bv =
+                            *reinterpret_cast<const u32x4 *>(hsl + (n * 16 + r) * kPitch + (32 * t + 8 * g) * 2);
+#pragma unroll
+                        for (int m = 0; m < 2; ++m) acc[m][n] = mfma_bf16(a[m], bv, acc[m][n]);
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+        // lane (r, g) holds rows 4 g + i of each 16-row tile for query 16 n + r:
+        // one 16-byte store where the four rows exist and are 16-byte aligned
+        // (non-temporal from 32 queries on; measured: a 16-query pass is
+        // faster with ordinary stores, a 32-query pass with non-temporal ones)
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int n = 0; n < NQT; ++n) {
+                const int q = n * 16 + r;
+                const int lr = rb + m * 16 + 4 * g;
+                if (q < nq) {
+                    float *zp = zout + (int64_t)q * V + r0 + lr;
+                    if (zvec && lr + 3 < nrows) {
+                        if constexpr (NQT == 1)
+                            *reinterpret_cast<f32x4 *>(zp) = acc[m][n];
+                        else
+                            __builtin_nontemporal_store(acc[m][n], reinterpret_cast<f32x4 *>(zp));
+                    } else
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (lr + i < nrows) zp[i] = acc[m][n][i];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (lr + i < nrows) topr_insert(make_key(acc[m][n][i], (int32_t)(r0 + lr + i)), best[n]);
+                }
+            }
+    }
+    // per query: the kTopR largest over the four lane groups, then over the waves
+#pragma unroll
+    for (int n = 0; n < NQT; ++n) {
+        topr_reduce<32, 16>(best[n]);
+        if (g == 0)
+#pragma unroll
+            for (int i = 0; i < kTopR; ++i) s_top[n * 16 + r][wave][i] = best[n][i];
+    }
+    __syncthreads();
+    if (tid < nq) {
+        uint64_t b[kTopR], o[kTopR];
+#pragma unroll
+        for (int i = 0; i < kTopR; ++i) b[i] = s_top[tid][0][i];
+        for (int w = 1; w < kMfmaWaves; ++w) {
+#pragma unroll
+            for (int i = 0; i < kTopR; ++i) o[i] = s_top[tid][w][i];
+            topr_merge(o, b);
+        }
+        store_topr(tops + ((int64_t)tid * gridDim.x + blockIdx.x) * kTopR, b);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// dense head, batches: skinny GEMM on the matrix cores, tiles through LDS
 // ---------------------------------------------------------------------------
 //
 // For several queries at once the slab logits come from the matrix cores, 16
@@ -938,8 +1222,8 @@ __global__ __launch_bounds__(kMergeThreads) void dense_merge_kernel(const float 
 // rounded to fp32 once, as on the vector path.
 //
 // The kernel streams W_out once, so it is bound by HBM as long as enough
-// bytes are in flight on every CU.  One workgroup of eight waves per CU owns
-// a contiguous run of rows and walks it in blocks of RT x 128 rows, each in
+// bytes are in flight on every CU.  One workgroup of eight waves per CU walks
+// its blocks of up to RT x 128 rows, each in
 // stages of KC = 256 / RT bytes of every row.  A stage (each wave's own RT x
 // 16 rows, and the same columns of the pass's queries for all waves) goes
 // from memory straight to LDS (global_load_lds, 16 bytes a lane), NBUF - 1
@@ -952,41 +1236,34 @@ __global__ __launch_bounds__(kMergeThreads) void dense_merge_kernel(const float 
 // stays in L2.
 //
 // The rows are divided evenly over the workgroups in units of four rows, so
-// no CU streams more than another however ragged the vocabulary.  A block's
+// no CU streams more than another however ragged the vocabulary.  A
+// workgroup's blocks are one run of rows, or (bf16) every blk_step-th block:
+// after W_out is written its last 256 MB lie dirty in the Infinity Cache, and
+// with runs these reads, which wait for write-backs, all fall to the same
+// third of the workgroups (128256 x 3072 bf16, 64 queries, first call on a new
+// W_out: 174 us with runs, 156 in turn).  A block's
 // logits (16-byte stores) and, per query and slab, the kTopR largest keys go
-// to the workspace in the layout of the single-query path, and
+// to the workspace, and
 // dense_merge_kernel selects the top k.  Ordering a slab's keys takes longer
 // than a stage, so a slab is all of a workgroup's blocks (64 queries of
 // 128256 x 3072 bf16: 162 us per call with a slab a block, 154 with one);
-// the merge's exact fallback serves the few slabs that hold kTopR of the top
-// k, and above k = 128, where they would be many, a workgroup ends up to four.
+// the merge reads the slabs that hold kTopR of the top k again, and above two
+// wanted keys a slab, where they would be many, a workgroup ends up to four.
 //
-// Measured per call with the merge (two matrices in turn; before, register-
-// staged slabs for bf16 and passes of eight queries on the vector ALUs for
-// fp32): 128256 x 2048 fp32, 16 queries 830 -> 203 us, 64 queries 3333 -> 578
-// us (four fifths of it at the fp64 matrix rate); 128256 x 3072 fp32, 4
-// queries 354 -> 294 us; 50257 x 1000 bf16, 5 queries 28.5 -> 24.7 us; 151936
-// x 1024 bf16, 8 / 64 queries 65.7 / 89 -> 60.4 / 85 us; 128256 x 3072 bf16,
-// 16 / 32 / 64 queries 133 / 140 / 155 -> 129 / 134 / 150 us.
+// fp32 rows, measured per call with the merge (two matrices in turn; before,
+// passes of eight queries on the vector ALUs): 128256 x 2048, 16 queries
+// 830 -> 203 us, 64 queries 3333 -> 578 us (four fifths of it at the fp64
+// matrix rate); 128256 x 3072, 4 queries 354 -> 294 us.
 
 constexpr int kTileWaves = 8;
 constexpr int kTileThreads = kTileWaves * kWave;
-constexpr int kTileMaxNB = 64;              // queries per pass
-constexpr int kTileMinB = 3;
 constexpr int kTileWgs = 256;               // one per CU
 constexpr int tile_rows(int RT) { return kTileWaves * 16 * RT; }        // most rows of a block
 constexpr int tile_kc(int RT) { return 256 / RT; }                      // bytes of a row per stage
 constexpr int tile_stage(int NQT, int RT) { return (tile_rows(RT) + 16 * NQT) * tile_kc(RT); }
 constexpr int tile_bufs(int NQT) { return NQT == 1 ? 4 : 3; }            // within 160 KB of LDS
 
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
-                                                   c, 0, 0, 0);
-}
 
 // 16 bytes per lane from src (per lane) to dst + 16 * lane (dst uniform over the wave)
 template <int AUX> __device__ __forceinline__ void load_lds16(const char *src, char *dst)
@@ -1001,7 +1278,8 @@ template <int KC> __device__ __forceinline__ int tile_swizzle(int x) { return KC
 template <bool BF16, int NQT, int RT, int AUX>
 __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void dense_tile_kernel(
     const char *__restrict__ W, int64_t V, int row_bytes, const char *__restrict__ hq, int nq, int rows_per_blk,
-    int blks_per_slab, int blks_per_wg, int nslab, float *__restrict__ zout, uint64_t *__restrict__ tops)
+    int blks_per_slab, int blks_per_wg, int nblks, int blk_step, int nslab, float *__restrict__ zout,
+    uint64_t *__restrict__ tops)
 {
     typedef typename std::conditional<BF16, f32x4, f64x4>::type Acc;
     extern __shared__ __align__(16) char smem[];
@@ -1017,15 +1295,18 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(2,
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int r = lane & 15, g = lane >> 4;
-    const int64_t r0 = (int64_t)blockIdx.x * blks_per_wg * rows_per_blk;
-    const int nrows = (int)min<int64_t>((int64_t)blks_per_wg * rows_per_blk, V - r0);
-    const int nblk = (nrows + rows_per_blk - 1) / rows_per_blk;
+    // this workgroup's blocks: blk0, blk0 + blk_step, ... (every workgroup has one)
+    const int blk0 = blk_step > 1 ? blockIdx.x : blockIdx.x * blks_per_wg;
+    int nblk = blks_per_wg;
+    while (blk0 + (nblk - 1) * blk_step >= nblks) --nblk;
+    auto first_row = [&](int b) { return (int64_t)(blk0 + b * blk_step) * rows_per_blk; };
+    auto block_rows = [&](int b) { return (int)min<int64_t>(rows_per_blk, V - first_row(b)); };
     const int nstage = (row_bytes + KC - 1) / KC;
     const bool ragged = row_bytes % KC != 0;
     const bool zvec = (V & 3) == 0 && ((uintptr_t)zout & 15) == 0;
 
-    // Staging.  A load covers four staged rows; lane l fills slot l % 16 of
-    // row l / 16 with the piece that belongs there.  Matrix row x of a wave
+    // Staging.  A load covers kLoadRows staged rows; lane l fills slot l %
+    // kPieces of row l / kPieces with the piece that belongs there.  Matrix row x of a wave
     // is its row x, or for fp32 rows row 4 (x % 4) + x / 4: a lane's four
     // results are four consecutive rows then (in fp64 they lie four apart).
     const char *wsrc[kWLoads], *hsrc[kHLoads];
@@ -1040,12 +1321,12 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(2,
         hcol[t] = 16 * (slot ^ tile_swizzle<KC>(x & 15));
     }
     auto set_block = [&](int b) {
-        const int last = min(rows_per_blk, nrows - b * rows_per_blk) - 1;
+        const int last = block_rows(b) - 1;
 #pragma unroll
         for (int t = 0; t < kWLoads; ++t) {
             const int x = kLoadRows * t + lrow;
             const int row = wave * 16 * RT + (BF16 ? x : (x & ~15) + 4 * (x % 4) + x % 16 / 4);
-            wsrc[t] = W + (r0 + (int64_t)b * rows_per_blk + min(row, last)) * row_bytes;
+            wsrc[t] = W + (first_row(b) + min(row, last)) * row_bytes;
         }
     };
     auto issue = [&](int st, int buf) {
@@ -1152,7 +1433,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(2,
             buf = buf == NBUF - 1 ? 0 : buf + 1;
         }
         // lane (r, g) holds rows 4 g + i of each row tile for query 16 n + r
-        const int live = min(rows_per_blk, nrows - b * rows_per_blk);  // rows of this block
+        const int live = block_rows(b);
         f32x4 z[RT][NQT];
 #pragma unroll
         for (int m = 0; m < RT; ++m)
@@ -1168,7 +1449,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(2,
         // the 93 us of 64 queries over 151936 x 1024 bf16; so, 85 us.)
         constexpr int kZPitch = kRows + 4;  // floats
         static_assert(kThrough == (16 * NQT * kZPitch * 4 <= kStage), "logits of a block in a stage");
-        float *zo = zout + r0 + (int64_t)b * rows_per_blk;
+        float *zo = zout + first_row(b);
         if constexpr (kThrough) {
             float *zl = reinterpret_cast<float *>(smem + (buf == 0 ? NBUF - 1 : buf - 1) * kStage);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -1214,7 +1495,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(2,
                 uint64_t key[kTopR];
 #pragma unroll
                 for (int i = 0; i < kTopR; ++i)
-                    key[i] = i < left ? make_key(z[m][n][i], (int32_t)(r0 + b * rows_per_blk + lr + i)) : 0ull;
+                    key[i] = i < left ? make_key(z[m][n][i], (int32_t)(first_row(b) + lr + i)) : 0ull;
                 sort4_desc(key);
                 if (m == 0 && b % blks_per_slab == 0) {
 #pragma unroll
@@ -1228,7 +1509,8 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(2,
         // end of a slab: per query the kTopR largest over the four lane
         // groups of each wave, then over the waves, one list a lane (32
         // queries at a time; barriers that leave the loads in flight)
-        const int slab = blockIdx.x * (blks_per_wg / blks_per_slab) + b / blks_per_slab;
+        const int slab = blk_step > 1 ? b / blks_per_slab * blk_step + blockIdx.x
+                                      : blockIdx.x * (blks_per_wg / blks_per_slab) + b / blks_per_slab;
 #pragma unroll
         for (int n0 = 0; n0 < NQT; n0 += 2) {
 #pragma unroll
@@ -3010,7 +3292,7 @@ hipError_t stream_launch(const void *W, int64_t V, int row_bytes, const char *h,
     kern<<<p.nwg, kDenseThreads, lds, s>>>(static_cast<const char *>(W), V, row_bytes, h, nq, p.rpw, zbuf, tops);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    dense_merge_kernel<<<nq, kMergeThreads, 0, s>>>(zbuf, tops, V, p.rpw, p.nwg, k, ids, logits);
+    dense_merge_kernel<<<nq, kMergeThreads, 0, s>>>(zbuf, tops, V, SlabRows{1, p.rpw, 1}, p.nwg, k, ids, logits);
     return hipGetLastError();
 }
 
@@ -3048,7 +3330,7 @@ hipError_t dense_launch(const void *W, int64_t V, int row_bytes, const char *h, 
     kern<<<p.nwg, kDenseThreads, lds, s>>>(static_cast<const char *>(W), V, row_bytes, h, nq, p.rpw, zbuf, tops);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    dense_merge_kernel<<<nq, kMergeThreads, 0, s>>>(zbuf, tops, V, p.rpw, p.nwg, k, ids, logits);
+    dense_merge_kernel<<<nq, kMergeThreads, 0, s>>>(zbuf, tops, V, SlabRows{1, p.rpw, 1}, p.nwg, k, ids, logits);
     return hipGetLastError();
 }
 
@@ -3069,42 +3351,120 @@ hipError_t dense_launch_nb(int nb, const void *W, int64_t V, int row_bytes, cons
 
 namespace {
 
-// Matrix-core plan: blocks of equal rows (a multiple of four, at most
-// tile_rows), the same number for each of at most kTileWgs workgroups, and
-// slabs of as many blocks as keep them within one thread each of the merge.
+// Register-staged plan: slabs of whole workgroup iterations, at most
+// kMfmaMaxWgs of them (the merge gives every slab a thread).
+DensePlan mfma_plan(int64_t V)
+{
+    const int64_t iters = (V + kMfmaRowsPerIter - 1) / kMfmaRowsPerIter;
+    const int64_t per = (iters + kMfmaMaxWgs - 1) / kMfmaMaxWgs;
+    DensePlan p;
+    p.rpw = (int)(per * kMfmaRowsPerIter);
+    p.nwg = (int)((V + p.rpw - 1) / p.rpw);
+    p.nbmax = kBatchMaxNB;
+    return p;
+}
+
+// Tile plan: blocks of equal rows (a multiple of four, at most tile_rows),
+// the same number for each of at most kTileWgs workgroups, and slabs of as
+// many blocks as keep them within one thread each of the merge.
 struct TilePlan {
-    int row_tiles, rows_per_blk, blks_per_slab, blks_per_wg, nwg, nslab;
+    int row_tiles, rows_per_blk, blks_per_slab, blks_per_wg, nblks, blk_step, nwg, nslab;
 };
 
-// Two row tiles a wave where a workgroup has the rows (128 or fewer would
-// leave half of it without), except for many bf16 queries: measured with two
-// against one, 128256 x 3072 bf16 134 against 137 us (16 queries) but 139
-// against 134 (32) and 161 against 154 (64); 128256 x 2048 fp32 207 against
-// 219 us (16) and 582 against 609 (64).  A slab: see above (k).
-TilePlan tile_plan(int64_t V, bool bf16, int nq, int k)
+// fp32 rows: two row tiles a wave where a workgroup has the rows (128 or fewer
+// would leave half of it without): 128256 x 2048 fp32 207 us with two, 219 with one
+// (16 queries), 582 and 609 (64); and one run of rows a workgroup (blocks in
+// turn: 128256 x 2048, 16 queries 252 us against 215).  bf16 rows: one row
+// tile, blocks in turn.  A slab: see above (k).
+TilePlan tile_plan(int64_t V, bool bf16, int k)
 {
     TilePlan p;
-    p.row_tiles = V > (int64_t)tile_rows(1) * kTileWgs && (!bf16 || nq <= 16) ? 2 : 1;
+    p.row_tiles = V > (int64_t)tile_rows(1) * kTileWgs && !bf16 ? 2 : 1;
     const int64_t round = (int64_t)tile_rows(p.row_tiles) * kTileWgs;
     int64_t per = (V + round - 1) / round;
-    const int slabs = k <= 128 ? 1 : kMergeThreads / kTileWgs;  // slabs of a workgroup, at most
+    const int slabs = k <= 2 * kTileWgs ? 1 : kMergeThreads / kTileWgs;  // slabs of a workgroup, at most
     p.blks_per_slab = (int)((per + slabs - 1) / slabs);
     per = (per + p.blks_per_slab - 1) / p.blks_per_slab * p.blks_per_slab;
     p.blks_per_wg = (int)per;
     p.rows_per_blk = (int)(((V + per * kTileWgs - 1) / (per * kTileWgs) + 3) / 4 * 4);
-    const int64_t slab_rows = (int64_t)p.rows_per_blk * p.blks_per_slab;
-    p.nwg = (int)((V + p.rows_per_blk * per - 1) / (p.rows_per_blk * per));
-    p.nslab = (int)((V + slab_rows - 1) / slab_rows);
+    p.nblks = (int)((V + p.rows_per_blk - 1) / p.rows_per_blk);
+    p.nwg = (int)((p.nblks + per - 1) / per);
+    p.blk_step = bf16 ? p.nwg : 1;
+    // (blocks in turn: the workgroups with a block in the last run of slabs)
+    const int full = p.blks_per_slab * p.nwg;
+    p.nslab = p.blk_step == 1 ? (p.nblks + p.blks_per_slab - 1) / p.blks_per_slab
+                              : p.nblks / full * p.nwg + std::min(p.nblks % full, p.nwg);
     return p;
 }
 
-bool use_tiles(int row_bytes, int B, const void *W, const void *h)
+// Batches of bf16 rows that take dense_tile_kernel; the others take the
+// register-staged kernel, of which two workgroups run on a CU.  The lines lie
+// where both kernels measured alike, at 110 heads of 1000 to 262144 rows by
+// 136 to 5120 columns and 3 to 64 queries, with W_out evicted from the caches
+// and with W_out just written (us per call with the merge, register-staged /
+// tiles):
+//   - heads that leave a quarter or more of the CUs without a register-staged
+//     workgroup: 16000 x 2048, 16 queries 28 / 24; 10000 x 3072, 64 queries 44 / 37;
+//   - heads whose last round of register-staged workgroups is mostly empty:
+//     151936 x 1024 (594 workgroups, 512 at a time), 5 / 64 queries 67 / 60 and 91 /
+//     80; 140000 x 3072, 33 queries 197 / 156; with few queries also those whose
+//     last round is less so, unless rows lie a multiple of 4 KB apart: 100352 x
+//     2560, 16 queries 102 / 93, but 190000 x 2048 148 / 163;
+//   - rows that are not whole 128-byte lines: two stages share a line, and plain
+//     loads find it in the caches (50257 x 1000, 16 queries 34 / 30; 262144 x 1000,
+//     33 queries 141 / 113), as long as rows are not short (45776 x 184, 33
+//     queries 21 / 24) nor, with few queries, the plain loads evict much of a
+//     W_out just written (262144 x 1000, 16 queries 124 / 135);
+//   - more than 16 queries against rows that outgrow the Infinity Cache:
+//     128256 x 3072, 64 queries 155 / 145, and 164 / 156 on a W_out just written;
+//     with more than 32 if most of a block's rows are there (99353 x 2432, 64
+//     queries, blocks of 100 rows, 123 / 126).
+// Elsewhere register-staged rows are faster: they read twice as much of a row
+// at a time, which counts most where rows lie a power of two apart (16
+// queries: 65536 x 4096 94 / 113, 128256 x 2048 105 / 117, 65536 x 1024 31 / 34).
+bool bf16_tiles(int64_t V, int row_bytes, int nq, int k)
 {
-    return B >= kTileMinB && row_bytes % 16 == 0 && (uintptr_t)W % 16 == 0 && (uintptr_t)h % 16 == 0;
+    constexpr int kAtOnce = 512;  // register-staged workgroups
+    const int wgs = mfma_plan(V).nwg, rounds = (wgs + kAtOnce - 1) / kAtOnce;
+    if (wgs <= 192 || wgs * kTopR < k) return true;  // (k: the merge takes its bound from the slabs' lists)
+    const bool lines = row_bytes % 128 == 0, large = V * row_bytes > (int64_t)256 << 20;
+    const bool empty = wgs * 20 <= rounds * kAtOnce * 13;  // at most 65% of the places taken
+    const bool partly = wgs * 5 <= rounds * kAtOnce * 4 && row_bytes % 4096 != 0;  // at most 80%
+    if (rounds == 1)
+        return row_bytes >= 512 && (lines ? empty && nq <= 32 : row_bytes >= 1024 || nq <= 16);
+    if (empty) return true;
+    if (nq <= 16) return large ? lines && partly : !lines || partly;
+    if (!lines) return true;
+    if (nq <= 32) return large || partly;
+    return large && tile_plan(V, true, k).rows_per_blk >= 112;
+}
+
+// The batch kernels: rows of 16-byte pieces, all 16-byte aligned.
+bool use_batch(int row_bytes, int B, const void *W, const void *h)
+{
+    return B >= kBatchMinB && row_bytes % 16 == 0 && (uintptr_t)W % 16 == 0 && (uintptr_t)h % 16 == 0;
 }
 
 // Queries per pass of either path.
-int dense_pass(int B) { return B >= kTileMinB ? kTileMaxNB : kDenseMaxNB; }
+int dense_pass(int B) { return B >= kBatchMinB ? kBatchMaxNB : kDenseMaxNB; }
+
+template <int NQT, int KC, int LA>
+hipError_t mfma_launch(const void *W, int64_t V, int d, const char *h, int nq, int k, const DensePlan &p,
+                       float *zbuf, uint64_t *tops, int32_t *ids, float *logits, hipStream_t s)
+{
+    auto kern = dense_mfma_kernel<NQT, KC, LA>;
+    constexpr size_t lds = mfma_lds(NQT, KC);
+    if (lds > 64 * 1024) {
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    kern<<<p.nwg, kMfmaThreads, lds, s>>>(static_cast<const uint16_t *>(W), V, d,
+                                           reinterpret_cast<const uint16_t *>(h), nq, p.rpw, zbuf, tops);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    dense_merge_kernel<<<nq, kMergeThreads, 0, s>>>(zbuf, tops, V, SlabRows{1, p.rpw, 1}, p.nwg, k, ids, logits);
+    return hipGetLastError();
+}
 
 template <bool BF16, int NQT, int RT, int AUX>
 hipError_t tile_launch(const void *W, int64_t V, int row_bytes, const char *h, int nq, int k, const TilePlan &p,
@@ -3115,11 +3475,11 @@ hipError_t tile_launch(const void *W, int64_t V, int row_bytes, const char *h, i
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     kern<<<p.nwg, kTileThreads, lds, s>>>(static_cast<const char *>(W), V, row_bytes, h, nq, p.rows_per_blk,
-                                          p.blks_per_slab, p.blks_per_wg, p.nslab, zbuf, tops);
+                                          p.blks_per_slab, p.blks_per_wg, p.nblks, p.blk_step, p.nslab, zbuf, tops);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    dense_merge_kernel<<<nq, kMergeThreads, 0, s>>>(zbuf, tops, V, p.rows_per_blk * p.blks_per_slab, p.nslab, k, ids,
-                                                    logits);
+    dense_merge_kernel<<<nq, kMergeThreads, 0, s>>>(zbuf, tops, V, SlabRows{p.blks_per_slab, p.rows_per_blk, p.blk_step},
+                                                    p.nslab, k, ids, logits);
     return hipGetLastError();
 }
 
@@ -3127,14 +3487,15 @@ template <bool BF16, int NQT>
 hipError_t tile_launch_form(const void *W, int64_t V, int row_bytes, const char *h, int nq, int k, const TilePlan &p,
                             float *zbuf, uint64_t *tops, int32_t *ids, float *logits, hipStream_t s)
 {
-    // A W_out that outgrows the 256 MB Infinity Cache is streamed past it
-    // (128256 x 3072 bf16, 64 queries: 154 us per call, 161 without), a
+    // W_out is streamed past the 256 MB Infinity Cache where it outgrows it
+    // (fp32) or would fill more than half of it (bf16, in turn with other
+    // memory: 128256 x 1024, 16 queries 56 us streamed, 61 through the cache), a
     // smaller one may still be there at the next call (50257 x 1000 bf16, 5
-    // queries: 25 us, 29 when streamed).
+    // queries: 28 us, 32 when streamed).  Lines that two stages share are not.
     constexpr int kNt = 2;
-    const bool nt = V * row_bytes > ((int64_t)256 << 20);
-    // (many bf16 queries run one row tile only)
-    if constexpr (!BF16 || NQT == 1)
+    const bool nt = BF16 ? row_bytes % 128 == 0 && V * row_bytes > (int64_t)128 << 20
+                         : V * row_bytes > (int64_t)256 << 20;
+    if constexpr (!BF16)
         if (p.row_tiles == 2)
             return nt ? tile_launch<BF16, NQT, 2, kNt>(W, V, row_bytes, h, nq, k, p, zbuf, tops, ids, logits, s)
                       : tile_launch<BF16, NQT, 2, 0>(W, V, row_bytes, h, nq, k, p, zbuf, tops, ids, logits, s);
@@ -3163,7 +3524,7 @@ size_t dense_workspace_bytes(int64_t V, int d, int B, int k)
     (void)k;
     const int pass = dense_pass(B);
     const int nb = B < pass ? B : pass;
-    const int slabs = dense_grid(V);  // tile_plan has no more
+    const int slabs = std::max(dense_grid(V), mfma_plan(V).nwg);  // (tile_plan has no more than dense_grid)
     return (((size_t)nb * V * 4 + 255) & ~(size_t)255) + (size_t)nb * slabs * 8 * kTopR;
 }
 
@@ -3181,16 +3542,23 @@ vie_status launch_dense_topk(const void *W, int dtype, int64_t V, int d, const v
     uint64_t *tops = reinterpret_cast<uint64_t *>(static_cast<char *>(ws) +
                                                    (((size_t)nbw * V * 4 + 255) & ~(size_t)255));
     const char *hb = static_cast<const char *>(h);
-    if (use_tiles(row_bytes, B, W, h)) {
-        for (int q0 = 0; q0 < B; q0 += kTileMaxNB) {
-            const int nq = B - q0 < kTileMaxNB ? B - q0 : kTileMaxNB;
-            const TilePlan tp = tile_plan(V, dtype == VIE_BF16, nq, k);
+    if (use_batch(row_bytes, B, W, h)) {
+        for (int q0 = 0; q0 < B; q0 += kBatchMaxNB) {
+            const int nq = B - q0 < kBatchMaxNB ? B - q0 : kBatchMaxNB;
             const char *hp = hb + (int64_t)q0 * row_bytes;
             int32_t *ip = ids + (int64_t)q0 * k;
             float *lp = logits + (int64_t)q0 * k;
-            const hipError_t e =
-                dtype == VIE_BF16 ? tile_launch_nq<true>(W, V, row_bytes, hp, nq, k, tp, zbuf, tops, ip, lp, s)
-                                  : tile_launch_nq<false>(W, V, row_bytes, hp, nq, k, tp, zbuf, tops, ip, lp, s);
+            hipError_t e;
+            if (dtype == VIE_F32) {
+                e = tile_launch_nq<false>(W, V, row_bytes, hp, nq, k, tile_plan(V, false, k), zbuf, tops, ip, lp, s);
+            } else if (bf16_tiles(V, row_bytes, nq, k)) {
+                e = tile_launch_nq<true>(W, V, row_bytes, hp, nq, k, tile_plan(V, true, k), zbuf, tops, ip, lp, s);
+            } else {
+                const DensePlan mp = mfma_plan(V);
+                e = nq <= 16   ? mfma_launch<1, VIE_MFMA_KC1, VIE_MFMA_LA1>(W, V, d, hp, nq, k, mp, zbuf, tops, ip, lp, s)
+                    : nq <= 32 ? mfma_launch<2, VIE_MFMA_KC2, VIE_MFMA_LA2>(W, V, d, hp, nq, k, mp, zbuf, tops, ip, lp, s)
+                               : mfma_launch<4, VIE_MFMA_KC4, VIE_MFMA_LA4>(W, V, d, hp, nq, k, mp, zbuf, tops, ip, lp, s);
+            }
             if (e != hipSuccess) return launched(e, "dense top-k (matrix cores) launch");
         }
         return VIE_OK;

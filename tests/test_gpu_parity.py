@@ -66,14 +66,14 @@ DENSE_CASES = [
     # batched bf16 on the matrix cores
     (20011, 256, synth.BF16, 16, 50),  # one 16-query tile, ragged slab tail
     (9000, 1000, synth.BF16, 33, 64),  # three query tiles padded to four, column tail
-    (9000, 1000, synth.BF16, 20, 64),  # two query tiles, stages loaded two ahead
-    (5000, 1400, synth.BF16, 24, 30),  # an odd number of 128-column stages, column tail
-    (2500, 40, synth.BF16, 20, 5),     # a row shorter than one 128-column step
+    (9000, 1000, synth.BF16, 20, 64),  # two query tiles, column tail
+    (5000, 1400, synth.BF16, 24, 30),  # an odd number of stages, column tail
+    (2500, 40, synth.BF16, 20, 5),     # a row shorter than one stage
     (3000, 64, synth.BF16, 130, 10),   # passes of 64, 64 and 2 queries
     (262147, 64, synth.BF16, 16, 20),  # several row blocks per slab
     (777, 37, synth.BF16, 17, 30),     # odd row: batched on the vector path
-    (4000, 96, synth.F32, 24, 40),     # fp32 batch: vector path, passes of 8
-    (1000, 64, synth.BF16, 16, 50),    # fewer slabs than k on the matrix-core path
+    (4000, 96, synth.F32, 24, 40),     # fp32 batch, two query tiles
+    (1000, 64, synth.BF16, 16, 50),    # 250 slabs of four rows
     # one or two queries over 16-byte aligned rows: the streaming slab kernel
     (30011, 640, synth.BF16, 1, 50),   # 80 chunks: the second chunk on 16 lanes only
     (12000, 1536, synth.BF16, 1, 64),  # 3 of 4 chunks per lane
@@ -133,6 +133,18 @@ def test_dense_topk_matches_oracle(vie, V, d, dtype, B, k):
     (66000, 24, synth.F32, 5, 1024),   # several slabs per workgroup
     (9001, 64, synth.BF16, 9, 900),    # most of the listed keys
     (300, 516, synth.F32, 3, 300),     # k = V: every listed key
+    # bf16, tiles with the blocks dealt to the workgroups in turn
+    (139999, 24, synth.BF16, 3, 20),   # five blocks, the last one on some workgroups only
+    (140003, 24, synth.BF16, 40, 600),  # three slabs of two blocks a workgroup, the last run short
+    (66000, 64, synth.BF16, 20, 1000),  # three slabs of one block a workgroup
+    (24577, 64, synth.BF16, 3, 800),   # one row past the heads that always take tiles: k does it
+    # bf16, register-staged rows
+    (24577, 64, synth.BF16, 3, 700),   # 193 slabs of 128 rows, one with a single row
+    (30001, 64, synth.BF16, 16, 50),
+    (26000, 192, synth.BF16, 24, 64),  # two query tiles, three stages of 128 columns, two ahead
+    (45000, 320, synth.BF16, 64, 30),  # four query tiles, a last stage of 64 columns
+    (120000, 128, synth.BF16, 5, 400),  # 938 slabs
+    (200003, 64, synth.BF16, 33, 900),  # slabs of two iterations, scalar logit stores
 ])
 def test_dense_batches_on_the_matrix_cores(vie, V, d, dtype, B, k):
     say("dense batch", V, d, dtype, B, k)
@@ -182,6 +194,29 @@ def test_dense_batch_time_does_not_jump_with_k(vie, dtype):
     assert took[300] < 4 * took[128], took
 
 
+@pytest.mark.parametrize("V,d,most", [(65536, 4096, 1.25), (262144, 1000, 1.5)])
+def test_a_small_bf16_batch_streams_like_one_query(vie, V, d, most):
+    # one pass over W_out either way: half a GB, which bounds both.  (Tiles for
+    # every batch took 1.4 and 1.8 times as long as one query here: rows a
+    # power of two apart, and rows that end inside a 128-byte line.)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    W = torch.empty(V, d, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    h = torch.randn(8, d, device="cuda", generator=g).bfloat16()
+    took = {}
+    for B in (1, 8, 1, 8):
+        head = vie.DenseHead(W, max_batch=B, max_k=50)
+        head(h[:B], 50)
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        for _ in range(30):
+            head(h[:B], 50)
+        torch.cuda.synchronize()
+        took[B] = min(took.get(B, 1.0), time.perf_counter() - t)
+    say("V=%d d=%d: one query %.1f us, eight %.1f us" % (V, d, took[1] / 30e-6, took[8] / 30e-6))
+    assert took[8] < most * took[1], took
+
+
 @pytest.mark.parametrize("B,k", [(1, 50), (1, 100), (16, 50), (16, 100), (16, 300), (1, 700)])
 def test_dense_far_maximum_takes_the_exact_fallbacks(vie, B, k):
     # one planted row per query scores about 2^20 times the usual maximum, so
@@ -207,11 +242,11 @@ def test_dense_far_maximum_takes_the_exact_fallbacks(vie, B, k):
     assert all(ids[b, 0] == 7 + 100 * b for b in range(B))
 
 
-@pytest.mark.parametrize("B", [1, 4])
-def test_dense_clustered_top_keys(vie, B):
+@pytest.mark.parametrize("B,V", [(1, 20000), (4, 20000), (4, 140003), (4, 50001)])
+def test_dense_clustered_top_keys(vie, B, V):
     # the best rows sit next to each other, so several slabs hold many of
     # the top k and must be read again (not just their largest key)
-    V, d, k = 20000, 128, 50
+    d, k = 128, 50
     W = synth.make_w(V, d, synth.BF16, 77)
     H, _ = synth.make_queries(W, synth.BF16, B, 78)
     Wf = synth.bf16_bits_to_f32(W).copy()
@@ -236,7 +271,7 @@ def test_dense_clustered_top_keys(vie, B):
 def test_dense_slab_lists_boundary(vie, B, dtype):
     # each slab passes its four largest keys to the merge; here single slabs
     # hold exactly 3, 4 and 5 of the top k (rows 2560 apart start a slab both
-    # for 20-row slabs of the vector path and 128-row slabs of the matrix
+    # for 20-row slabs of the vector path and 80-row slabs of the matrix
     # cores), so the merge takes a list whole, must read a slab whose fourth
     # key clears the threshold, and must find a fifth key outside the list
     V, d, k = 20000, 128, 20
@@ -257,16 +292,18 @@ def test_dense_slab_lists_boundary(vie, B, dtype):
     parity.check_id_sets(W, dtype, H, ids, oid, osc[:, -1], what="slab lists")
 
 
-@pytest.mark.parametrize("V,k", [(30000, 64), (200000, 100)])
-def test_dense_zero_query_orders_by_id(vie, V, k):
+@pytest.mark.parametrize("V,k,B", [(30000, 64, 1), (200000, 100, 1), (140003, 100, 3), (140003, 700, 3),
+                                   (50000, 100, 3)])
+def test_dense_zero_query_orders_by_id(vie, V, k, B):
     # every logit is 0, so the answer is ids 0..k-1 (ties go to the smaller
-    # id); the second case has more tied keys at the threshold than the
-    # merge holds in LDS, which takes its bisection path
+    # id); all but the first case have more tied keys at the threshold than
+    # the merge holds in LDS, which takes its bisection path (the batches:
+    # over slabs of blocks that lie apart, and of register-staged rows)
     W = synth.make_w(V, 32, synth.BF16, 5)
-    head = vie.DenseHead(dev_tensor(vie, W, synth.BF16), max_batch=1, max_k=k)
-    ids, lg = head(torch.zeros((1, 32), dtype=torch.bfloat16, device="cuda"), k)
+    head = vie.DenseHead(dev_tensor(vie, W, synth.BF16), max_batch=B, max_k=k)
+    ids, lg = head(torch.zeros((B, 32), dtype=torch.bfloat16, device="cuda"), k)
     torch.cuda.synchronize()
-    assert ids.cpu().numpy()[0].tolist() == list(range(k))
+    assert (ids.cpu().numpy() == np.arange(k)).all()
     assert np.all(lg.cpu().numpy() == 0)
 
 
