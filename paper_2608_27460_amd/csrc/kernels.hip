@@ -35,6 +35,7 @@
 
 #include "index.hpp"
 #include "keys.hpp"
+#include "team.hpp"
 
 namespace vie {
 
@@ -1659,7 +1660,6 @@ struct TeamArgs {
     int line;
     uint64_t *keys;   // of a query: keys of set 0, of set 1, then the lines of both sets
 };
-constexpr uint64_t kTeamMark = 1ull << 31;
 constexpr int kTeamWords = 2 * 1024;  // words of a set's lines, at most: two per thread
 
 // Waits of a team member at an exchange are bounded (about two seconds):
@@ -2441,7 +2441,7 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
     auto exchange = [&](uint32_t mine, uint32_t fresh, uint64_t *dst) -> int {
         const uint64_t *keys = team_keys();
         uint64_t *lines = team.keys + ((int64_t)q * 3 + 2) * T * team.slot + (int64_t)(exchanges & 1u) * T * L;
-        const uint64_t mark = exchanges & 2u ? 0ull : kTeamMark;
+        const uint64_t mark = team_mark(exchanges);
         ++exchanges;
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
         if (mine >= (uint32_t)L) {  // uniform
@@ -2465,13 +2465,9 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
         }
         uint32_t spins = 0;
         while (need) {
-#pragma unroll
-            for (int i = 0; i < kPerThread; ++i)
-                if (need & (1u << i))
-                    v[i] = __hip_atomic_load(lines + tid + i * NT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-            for (int i = 0; i < kPerThread; ++i)
-                if ((v[i] & kTeamMark) == mark) need &= ~(1u << i);
+            need = team_poll(need, mark, v, [&](int i) {
+                return __hip_atomic_load(lines + tid + i * NT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            });
             if (!need) break;
             if (++spins > kTeamSpin) {
                 sh.team_err = 1;
@@ -2480,20 +2476,15 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
             __builtin_amdgcn_s_sleep(1);
         }
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
-#pragma unroll
-        for (int i = 0; i < kPerThread; ++i) {
-            const int w = tid + i * NT, o = w >> lshift;
-            if (w >= T * L) continue;
-            if ((w & (L - 1)) == 0) {  // a header (0 for this member)
-                n_other += (uint32_t)(v[i] >> 32);
-                const uint32_t c = (uint32_t)v[i] & 0x7FFFFFFFu;
+        team_sift(
+            v, need, tid, NT, T * L, lshift,
+            [&](int o, uint32_t new_nodes, uint32_t c) {  // a header (0 for this member)
+                n_other += new_nodes;
                 const uint32_t over = c >= (uint32_t)L ? c - (uint32_t)(L - 1) : 0u;
                 s_xoff[o] = over ? atomicAdd(&sh.nx, over) << 16 | over : 0u;
                 if (over) sh.nover = 1;
-            } else if ((uint32_t)v[i] & 0x7FFFFFFFu) {
-                dst[mine + atomicAdd(&sh.nx, 1u)] = v[i] | kTeamMark;
-            }
-        }
+            },
+            [&](uint64_t key) { dst[mine + atomicAdd(&sh.nx, 1u)] = key; });
         __syncthreads();
         if (sh.team_err) return 0;
         if (sh.nover) {  // uniform: the keys beyond the lines, NT / T threads a member
