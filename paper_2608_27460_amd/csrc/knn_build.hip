@@ -33,6 +33,7 @@
 
 #include "index.hpp"
 #include "keys.hpp"
+#include "knn_form.hpp"
 
 namespace vie {
 
@@ -423,12 +424,6 @@ static_assert(kPairLoads * kPairThreads * 16 == kPairStage, "staging shape");
 static_assert(kPairTileC % (kPairThreads / 4) == 0, "one load covers rows c or rows j, never both");
 constexpr int kPairLds = kPairBufs * kPairStage + kPairRows * 4;
 constexpr int kPairList = kPairBufs * kPairStage / 8 / (kPairThreads / kWave);  // listed scores per wave
-constexpr int kPairCap = 1024;        // keys kept per row
-// Heads from this many rows on take this form: per build, against the chunked
-// form, 6000 / 12000 / 20000 / 32768 rows of 256 fp32 values took 3.9 / 5.4 /
-// 7.4 / 11.7 ms (3.5 / 5.2 / 8.2 / 14.8), of 1024 bf16 values 4.2 / 4.7 / 6.1 /
-// 8.9 ms (4.3 / 4.6 / 6.8 / 11.6): below, the sampling costs what it saves.
-constexpr int kPairMinRows = 16384;
 constexpr int kPairPickRows = 4096;   // sampled rows, at least (or V)
 constexpr int kPairPickStep = 32;     // sampled rows, at least one in this many
 
@@ -1267,16 +1262,9 @@ vie_status build_knn_graph_gpu(const void *W_dev, int dtype, int64_t V, int d, i
                                hipStream_t s, Graph &g, DeviceGraph &dg)
 {
     const int row_bytes = d * elem_bytes(dtype);
-    // Scores of all pairs at once (knn_pairs_kernel) unless the caller bounds
-    // the scores in memory, the keys would pass 4 GiB, or the head is small
-    // enough for the chunked form.
-    const bool pairs = chunk_rows == 0 && V >= kPairMinRows && V * (int64_t)(kPairCap * 8) <= ((int64_t)4 << 30);
-    const int64_t ld = (V + 3) & ~(int64_t)3;  // 16-byte aligned rows of scores
-    int64_t R = chunk_rows > 0 ? chunk_rows : ((int64_t)2 << 30) / (ld * 4);
-    if (pairs) R = V * (int64_t)(kPairCap * 8) / (ld * 4);  // the rows left over, in the keys' memory
-    R = std::max<int64_t>(1, std::min<int64_t>(R, V));
-    if (R * ld > ((int64_t)1 << 31)) return fail(VIE_EUNSUPPORTED, "GPU build: a score chunk of %lld rows is too large", (long long)R);
-    const size_t score_bytes = pairs ? (size_t)V * kPairCap * 8 : (size_t)R * ld * 4;
+    KnnForm form = knn_form(V, chunk_rows, true);
+    if (form.chunk * form.ld > ((int64_t)1 << 31))
+        return fail(VIE_EUNSUPPORTED, "GPU build: a score chunk of %lld rows is too large", (long long)form.chunk);
     int dev = 0;
     hipError_t he = hipGetDevice(&dev);
     if (he != hipSuccess) return fail(VIE_EHIP, "hipGetDevice: %s", hipGetErrorString(he));
@@ -1294,9 +1282,9 @@ vie_status build_knn_graph_gpu(const void *W_dev, int dtype, int64_t V, int d, i
     const int pick_step = (int)std::max<int64_t>(1, std::min<int64_t>(kPairPickStep, V / kPairPickRows));
     const int64_t npick = (V + pick_step - 1) / pick_step;
     // laid out twice: for the size, then in the allocation
-    auto lay_out = [&]() {
+    auto lay_out = [&](const KnnForm &f) {
         b.bytes = 0;
-        b.part(b.S, score_bytes);
+        b.part(b.S, f.score_bytes);
         b.part(b.cand, (size_t)V * K * 4);
         b.part(b.cand_score, (size_t)V * K * 4);
         b.part(b.fwd, (size_t)edges * 4);
@@ -1307,23 +1295,29 @@ vie_status build_knn_graph_gpu(const void *W_dev, int dtype, int64_t V, int d, i
         b.part(b.rev, (size_t)edges * 8);
         b.part(b.best, 8);
         b.part(b.sample, (size_t)(nreg + 1) * row_bytes);
-        if (pairs) {
+        if (f.pairs) {
             b.part(b.pick, (size_t)npick * row_bytes);
             b.part(b.thr, (size_t)V * 4);
             b.part(b.nleft, 4);
             b.part(b.left, (size_t)V * 4);
         }
     };
-    lay_out();
-    bool ok = dalloc(b.scratch, b.bytes);
-    if (ok) lay_out();
-    ok = ok && dalloc(b.adj0, (size_t)edges * 4) && dalloc(b.upper_off, (size_t)V * 4) && dalloc(b.upper, 4);
-    if (!ok) {
-        b.release();
-        b.release_graph();
+    const bool ok = knn_first_form(V, chunk_rows, form, [&](const KnnForm &f) {
+        lay_out(f);
+        bool fits = dalloc(b.scratch, b.bytes);
+        if (fits) lay_out(f);
+        fits = fits && dalloc(b.adj0, (size_t)edges * 4) && dalloc(b.upper_off, (size_t)V * 4) && dalloc(b.upper, 4);
+        if (!fits) {
+            b.release();
+            b.release_graph();
+        }
+        return fits;
+    });
+    if (!ok)
         return fail(VIE_ENOMEM, "GPU build: device allocation failed (V = %lld, chunk of %lld rows)", (long long)V,
-                    (long long)R);
-    }
+                    (long long)form.chunk);
+    const bool pairs = form.pairs;
+    const int64_t ld = form.ld, R = form.chunk;
     auto bail = [&](vie_status st) {
         (void)hipStreamSynchronize(s);
         b.release();
@@ -1394,7 +1388,7 @@ vie_status build_knn_graph_gpu(const void *W_dev, int dtype, int64_t V, int d, i
         he = hipMemcpy2DAsync(b.pick, (size_t)row_bytes, W, (size_t)pick_step * row_bytes, (size_t)row_bytes,
                               (size_t)npick, hipMemcpyDeviceToDevice, s);
         const int64_t pld = (npick + 3) & ~(int64_t)3;
-        const int64_t PR = std::min<int64_t>(V, (int64_t)(score_bytes / (pld * 4)));
+        const int64_t PR = std::min<int64_t>(V, (int64_t)(form.score_bytes / (pld * 4)));
         const double mean = (double)K * npick / V;
         // (at most 55: from kPairMinRows rows on at most one row in four is sampled)
         const int want = std::min(kWave, (int)std::ceil(mean + 3.5 * std::sqrt(mean) + 2.0));

@@ -7,9 +7,10 @@
   ABI by tests/sanitize/host_driver.cpp: the multithreaded builder, the
   index file with corrupt and truncated copies, export, and the error paths,
   among them an allocation failure that must give VIE_ENOMEM without a leak.
-- The rules by which the members of a team search read each other's words
-  (team.hpp, which the kernel uses) run on plain memory, also where a member
-  stops (tests/sanitize/team_words.cpp).
+- Rules that the device code takes from headers run on the host: how the
+  members of a team search read each other's words, also where a member stops
+  (tests/sanitize/team_words.cpp), and which form a graph build takes when
+  device memory is short (tests/sanitize/knn_form.cpp).
 - The oracle (oracle/oracle.c) is built with AddressSanitizer +
   UndefinedBehaviorSanitizer and runs every entry point on small inputs in
   a child Python process with the sanitizer runtimes preloaded.
@@ -83,14 +84,16 @@ def test_host_runtime_tsan(tmp_path):
     assert "all checks passed" in _run([exe, str(scratch)], env)
 
 
-def test_team_words_after_a_wait_that_gave_up(tmp_path):
-    # the rules by which a team member takes the others' keys, on the host: a
-    # member that stops must not leave keys of an earlier exchange to be taken
+@pytest.mark.parametrize("name", [
+    "team_words",  # a team member that stops must not leave keys of an earlier exchange to be taken
+    "knn_form",    # a graph build whose keys do not fit takes the chunked form
+])
+def test_device_rules_on_the_host(tmp_path, name):
     if not shutil.which("g++"):
         pytest.skip("no host compiler")
-    exe = str(tmp_path / "team_words")
+    exe = str(tmp_path / name)
     r = subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-Wall", "-Wno-unknown-pragmas", "-I", CSRC,
-                        os.path.join(SAN, "team_words.cpp"), "-o", exe], capture_output=True, text=True)
+                        os.path.join(SAN, name + ".cpp"), "-o", exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-4000:]
     assert "all checks passed" in _run([exe])
 
