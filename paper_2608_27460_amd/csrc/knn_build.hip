@@ -392,10 +392,14 @@ __global__ __launch_bounds__(kGramThreads) __attribute__((amdgpu_waves_per_eu(2)
 // unordered pair of rows is multiplied once, in 256 x 128 tiles of the upper
 // triangle, and no score reaches HBM: a score that reaches the threshold of
 // either of its rows is appended, as a key, to the keys of that row.  A
-// row's threshold is a sampled score (knn_threshold_kernel) with about three
-// times K scores above it; a row whose keys turn out fewer than K or more
+// row's threshold is a sampled score (knn_threshold_kernel) with about 1.7 (one
+// row in four sampled) to 3.3 times K scores above it (one in 32, K = 128); a
+// row whose keys turn out fewer than K or more
 // than kPairCap is left to the chunked form, so the sample decides the speed
-// only, never the result.
+// only, never the result.  Where the sample shows that half of the rows would
+// be left (equal scores without number), the pairs are not multiplied at all
+// (a build over 32768 x 256 bf16 zeros: 38.1 ms
+// with them, 23.6 without, 23.5 in the chunked form).
 //
 // Bound by the matrix cores.  151936 x 1024 bf16: 25.5 ms for 23.6 TFLOP (0.93
 // PFLOP/s; an 8192-cubed library product reaches 1.21), where the chunked form
@@ -438,10 +442,11 @@ __device__ __forceinline__ void pair_append(int64_t row, uint64_t key, uint32_t 
 
 template <bool BF16>
 __global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void knn_pairs_kernel(
-    const char *__restrict__ W, int64_t V, int row_bytes, int sb, const float *__restrict__ thr, uint32_t *count,
-    uint64_t *keys)
+    const char *__restrict__ W, int64_t V, int row_bytes, int sb, const float *__restrict__ thr,
+    const uint32_t *__restrict__ full, uint32_t *count, uint64_t *keys)
 {
     extern __shared__ __align__(16) char smem[];
+    if (*full > (uint32_t)(V / 2)) return;  // most rows would take too many keys
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int r = lane & 15, g = lane >> 4;
@@ -608,9 +613,31 @@ __global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(4,
     }
 }
 
-// Threshold of each row of a chunk from its scores against the sampled rows
-// (sampled row p is row p * step of W_out): the want-th largest (want <= 64),
-// the row itself left out.  One wave per row, no barrier: the want-th largest
+// The p-th sampled row: one of the rows p * step .. p * step + step - 1, drawn
+// by a hash of p (rows that repeat with a period of the step would all be the
+// same kind of row otherwise, and no threshold serve: 65536 x 512 bf16 in 64
+// interleaved clusters: 27.4 ms a build with every 32nd row, 7.1).
+__device__ __forceinline__ int64_t sampled_row(int64_t p, int step, int64_t V)
+{
+    const uint32_t h = (uint32_t)p * 0x9E3779B1u;
+    return p * step + (h >> 16) % (uint32_t)min<int64_t>(step, V - p * step);
+}
+
+// The sampled rows of W_out, gathered (one workgroup a row).
+__global__ __launch_bounds__(256) void knn_sample_kernel(const char *__restrict__ W, int64_t V, int row_bytes, int step,
+                                                         char *__restrict__ pick)
+{
+    const int64_t p = blockIdx.x;
+    const u32x4 *src = reinterpret_cast<const u32x4 *>(W + sampled_row(p, step, V) * row_bytes);
+    u32x4 *dst = reinterpret_cast<u32x4 *>(pick + p * row_bytes);
+    for (int c = threadIdx.x; c < row_bytes / 16; c += blockDim.x) dst[c] = src[c];
+}
+
+// Threshold of each row of a chunk from its scores against the sampled rows:
+// the want-th largest (want <= 64),
+// the row itself left out; *full counts the rows whose threshold is reached by
+// so many sampled scores that they would take more than twice kPairCap keys.
+// One wave per row, no barrier: the want-th largest
 // of the 64 lanes' maxima has at least `want` scores at or above it; those
 // are listed and ranked (more than kThrCap of them, equal scores: that bound
 // itself, still a valid threshold).  Bound by its two reads of the scores, the
@@ -620,15 +647,16 @@ constexpr int kThrWaves = 4;
 constexpr int kThrCap = 512;
 
 __global__ __launch_bounds__(kThrWaves *kWave) void knn_threshold_kernel(const float *__restrict__ S, int64_t ld,
-                                                                        int64_t r0, int64_t rows, int64_t np, int step,
-                                                                        int want, float *__restrict__ thr)
+                                                                        int64_t r0, int64_t rows, int64_t V, int64_t np,
+                                                                        int step, int want, float *__restrict__ thr,
+                                                                        uint32_t *__restrict__ full)
 {
     __shared__ uint32_t s_list[kThrWaves][kThrCap];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int64_t rr = (int64_t)blockIdx.x * kThrWaves + wave;
     if (rr >= rows) return;
     const int64_t i = r0 + rr;
-    const int64_t self = i % step == 0 ? i / step : -1;  // the row's own place in the sample
+    const int64_t self = sampled_row(i / step, step, V) == i ? i / step : -1;  // the row's own place in the sample
     const f32x4 *row = reinterpret_cast<const f32x4 *>(S + rr * ld);  // (rows of scores start 16-byte aligned)
     const int64_t n4 = (np + 3) / 4;  // scores past np are in the row's padding, left out below
     // order bits of the scores 4 c .. 4 c + 3 (0 for those left out: no score has these bits but a NaN)
@@ -679,10 +707,14 @@ __global__ __launch_bounds__(kThrWaves *kWave) void knn_threshold_kernel(const f
         }
     }
     if (m > (uint32_t)kThrCap) {
-        if (lane == 0) thr[i] = ord2f(lo);
+        if (lane == 0) {
+            thr[i] = ord2f(lo);
+            if (m * (uint32_t)step > 2u * kPairCap) atomicAdd(full, 1u);
+        }
         return;
     }
     __builtin_amdgcn_wave_barrier();
+    bool found = false;
     for (uint32_t t = lane; t < m; t += kWave) {
         const uint32_t v = list[t];
         int above = 0, equal = 0;
@@ -690,7 +722,13 @@ __global__ __launch_bounds__(kThrWaves *kWave) void knn_threshold_kernel(const f
             above += list[u] > v;
             equal += list[u] == v;
         }
-        if (above < want && want <= above + equal) thr[i] = ord2f(v);  // (equal scores write the same)
+        // (one lane, or several with equal scores, also 64 places on)
+        const uint64_t at = __ballot(above < want && want <= above + equal);
+        if (!found && at != 0ull && lane == __ffsll((long long)at) - 1) {
+            thr[i] = ord2f(v);
+            if ((above + equal) * step > 2 * kPairCap) atomicAdd(full, 1u);
+        }
+        found |= at != 0ull;
     }
 }
 
@@ -1222,7 +1260,7 @@ struct Buffers {
     char *sample = nullptr;  // the rows of W_out the fingerprint samples, gathered
     char *pick = nullptr;    // the rows the thresholds are sampled from, gathered
     float *thr = nullptr;    // threshold of every row
-    uint32_t *nleft = nullptr;
+    uint32_t *nleft = nullptr;  // number of rows left, then of rows whose sample has too many keys
     int32_t *left = nullptr;  // rows whose threshold did not serve
     // a part of n bytes at the end of the scratch (256-byte aligned)
     template <typename T> void part(T *&p, size_t n)
@@ -1298,7 +1336,7 @@ vie_status build_knn_graph_gpu(const void *W_dev, int dtype, int64_t V, int d, i
         if (f.pairs) {
             b.part(b.pick, (size_t)npick * row_bytes);
             b.part(b.thr, (size_t)V * 4);
-            b.part(b.nleft, 4);
+            b.part(b.nleft, 8);
             b.part(b.left, (size_t)V * 4);
         }
     };
@@ -1385,8 +1423,11 @@ vie_status build_knn_graph_gpu(const void *W_dev, int dtype, int64_t V, int d, i
         const char *W = static_cast<const char *>(W_dev);
         uint64_t *keys = reinterpret_cast<uint64_t *>(b.S);
         // sampled scores of every row, in the keys' memory
-        he = hipMemcpy2DAsync(b.pick, (size_t)row_bytes, W, (size_t)pick_step * row_bytes, (size_t)row_bytes,
-                              (size_t)npick, hipMemcpyDeviceToDevice, s);
+        he = hipMemsetAsync(b.nleft, 0, 8, s);
+        if (he == hipSuccess) {
+            knn_sample_kernel<<<(unsigned)npick, 256, 0, s>>>(W, V, row_bytes, pick_step, b.pick);
+            he = hipGetLastError();
+        }
         const int64_t pld = (npick + 3) & ~(int64_t)3;
         const int64_t PR = std::min<int64_t>(V, (int64_t)(form.score_bytes / (pld * 4)));
         const double mean = (double)K * npick / V;
@@ -1397,11 +1438,10 @@ vie_status build_knn_graph_gpu(const void *W_dev, int dtype, int64_t V, int d, i
             he = launch_gram(nullptr, r0, rows, b.pick, npick, pld);
             if (he != hipSuccess) break;
             knn_threshold_kernel<<<(unsigned)((rows + kThrWaves - 1) / kThrWaves), kThrWaves * kWave, 0, s>>>(
-                b.S, pld, r0, rows, npick, pick_step, want, b.thr);
+                b.S, pld, r0, rows, V, npick, pick_step, want, b.thr, b.nleft + 1);
             he = hipGetLastError();
         }
         if (he == hipSuccess) he = hipMemsetAsync(b.count, 0, (size_t)V * 4, s);
-        if (he == hipSuccess) he = hipMemsetAsync(b.nleft, 0, 4, s);
         if (he == hipSuccess) {
             const int64_t nt = (V + kPairTileC - 1) / kPairTileC;
             const int sb = nt >= 64 ? 8 : nt >= 16 ? 4 : 1;
@@ -1410,7 +1450,7 @@ vie_status build_knn_graph_gpu(const void *W_dev, int dtype, int64_t V, int d, i
             auto kern = dtype == VIE_BF16 ? knn_pairs_kernel<true> : knn_pairs_kernel<false>;
             he = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kPairLds);
             if (he == hipSuccess) {
-                kern<<<(unsigned)wgs, kPairThreads, kPairLds, s>>>(W, V, row_bytes, sb, b.thr, b.count, keys);
+                kern<<<(unsigned)wgs, kPairThreads, kPairLds, s>>>(W, V, row_bytes, sb, b.thr, b.nleft + 1, b.count, keys);
                 he = hipGetLastError();
             }
         }
@@ -1422,7 +1462,8 @@ vie_status build_knn_graph_gpu(const void *W_dev, int dtype, int64_t V, int d, i
         if (he == hipSuccess) host_part();
         if (he == hipSuccess) he = hipMemcpyAsync(&nleft, b.nleft, 4, hipMemcpyDeviceToHost, s);
         if (he == hipSuccess) he = hipStreamSynchronize(s);
-        if (he == hipSuccess && nleft > 0) he = chunked(b.left, nleft);
+        // (all of them: in their own order, a row of W_out after the other)
+        if (he == hipSuccess && nleft > 0) he = chunked(nleft == V ? nullptr : b.left, nleft);
     } else {
         he = chunked(nullptr, V);
     }
