@@ -175,6 +175,26 @@ def test_pair_form_is_not_slower_than_the_chunked_form(vie, V, d, rows):
     assert took[0] < 1.2 * took[chunk], took
 
 
+@pytest.mark.parametrize("V,d,dtype,K,M0", [
+    (140003, 16, synth.BF16, 64, 32),   # one row in 32 sampled; 547 row tiles, the last one ragged
+    (131073, 8, synth.F32, 128, 64),    # one row in the last tile
+    (300001, 8, synth.BF16, 16, 8),     # 2.3 GiB of keys
+])
+def test_pair_form_of_large_heads_equals_the_chunked_form(vie, V, d, dtype, K, M0):
+    # the triangle of tiles over many blocks, dealt to the XCDs: a tile left
+    # out would lose neighbours that the chunked form, which multiplies every
+    # row with every row, finds
+    say("gpu build (pairs, large)", V, d, dtype, K, M0)
+    Wf = np.random.default_rng(V).standard_normal((V, d)).astype(np.float32)
+    Wd = vie.host_to_torch(Wf if dtype == synth.F32 else vie_bits(Wf), dtype).cuda()
+    a = vie.Index.build_gpu(Wd, K, M0)
+    b = vie.Index.build_gpu(Wd, K, M0, chunk_rows=(1 << 30) // (4 * V))
+    torch.cuda.synchronize()
+    assert a.info()["entry"] == b.info()["entry"]
+    bad = np.nonzero(np.any(a.export()["adj0"] != b.export()["adj0"], axis=1))[0]
+    assert len(bad) == 0, "lists differ at %d nodes, first %s" % (len(bad), bad[:5])
+
+
 def vie_bits(Wf):
     # torch's cast keeps NaN and infinity
     return torch.from_numpy(Wf).bfloat16().view(torch.int16).numpy().view(np.uint16)
