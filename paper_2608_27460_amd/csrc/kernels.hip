@@ -3395,7 +3395,8 @@ TilePlan tile_plan(int64_t V, bool bf16, int k)
 // and with W_out just written (us per call with the merge, register-staged /
 // tiles):
 //   - heads that leave a quarter or more of the CUs without a register-staged
-//     workgroup: 16000 x 2048, 16 queries 28 / 24; 10000 x 3072, 64 queries 44 / 37;
+//     workgroup (any, up to 32 queries): 16000 x 2048, 16 queries 28 / 24; 10000 x
+//     3072, 64 queries 44 / 37; 32768 x 128, 3 queries 12.0 / 11.4;
 //   - heads whose last round of register-staged workgroups is mostly empty:
 //     151936 x 1024 (594 workgroups, 512 at a time), 5 / 64 queries 67 / 60 and 91 /
 //     80; 140000 x 3072, 33 queries 197 / 156; with few queries also those whose
@@ -3417,7 +3418,7 @@ bool bf16_tiles(int64_t V, int row_bytes, int nq, int k)
 {
     constexpr int kAtOnce = 512;  // register-staged workgroups
     const int wgs = mfma_plan(V).nwg, rounds = (wgs + kAtOnce - 1) / kAtOnce;
-    if (wgs <= 192 || wgs * kTopR < k) return true;  // (k: the merge takes its bound from the slabs' lists)
+    if (wgs <= (nq <= 32 ? 256 : 192) || wgs * kTopR < k) return true;  // (k: the merge's bound comes from the lists)
     const bool lines = row_bytes % 128 == 0, large = V * row_bytes > (int64_t)256 << 20;
     const bool empty = wgs * 20 <= rounds * kAtOnce * 13;  // at most 65% of the places taken
     const bool partly = wgs * 5 <= rounds * kAtOnce * 4 && row_bytes % 4096 != 0;  // at most 80%
