@@ -428,6 +428,9 @@ static_assert(kPairLoads * kPairThreads * 16 == kPairStage, "staging shape");
 static_assert(kPairTileC % (kPairThreads / 4) == 0, "one load covers rows c or rows j, never both");
 constexpr int kPairLds = kPairBufs * kPairStage + kPairRows * 4;
 constexpr int kPairList = kPairBufs * kPairStage / 8 / (kPairThreads / kWave);  // listed scores per wave
+// squares of 256 rows on a side of a launch block: 151936 x 1024 bf16 43.0 ms a
+// build with 8, 42.9 with 4, 44.2 with 16; 32768 x 256 fp32 7.03, 7.04 and 7.42
+constexpr int kPairBlock = 8;
 constexpr int kPairPickRows = 4096;   // sampled rows, at least (or V)
 constexpr int kPairPickStep = 32;     // sampled rows, at least one in this many
 
@@ -442,7 +445,7 @@ __device__ __forceinline__ void pair_append(int64_t row, uint64_t key, uint32_t 
 
 template <bool BF16>
 __global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void knn_pairs_kernel(
-    const char *__restrict__ W, int64_t V, int row_bytes, int sb, const float *__restrict__ thr,
+    const char *__restrict__ W, int64_t V, int row_bytes, const float *__restrict__ thr,
     const uint32_t *__restrict__ full, uint32_t *count, uint64_t *keys)
 {
     extern __shared__ __align__(16) char smem[];
@@ -451,12 +454,14 @@ __global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(4,
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int r = lane & 15, g = lane >> 4;
     const int wm = wave / kPairWavesJ, wn = wave % kPairWavesJ;
-    // Launch order: blocks of sb x sb squares of kPairTileC rows, walked over
-    // the upper triangle and dealt to the XCDs in turn (workgroup L runs on
+    // Launch order: blocks of kPairBlock x kPairBlock squares of kPairTileC
+    // rows, walked over the upper triangle and dealt to the XCDs in turn (workgroup L runs on
     // XCD L % 8), so that the tiles an XCD works on at a time share their
     // rows in its L2.  Workgroups past the triangle return at once.
     constexpr int F = kPairTileC / kPairTileJ;
-    const uint32_t per = (uint32_t)(sb * sb * F), i0 = blockIdx.x >> 3;
+    constexpr int sb = kPairBlock;
+    constexpr uint32_t per = (uint32_t)(sb * sb * F);
+    const uint32_t i0 = blockIdx.x >> 3;
     const uint32_t blk = (i0 / per) * 8 + (blockIdx.x & 7), in = i0 % per;
     uint32_t bj = (uint32_t)((sqrtf(8.0f * (float)blk + 1.0f) - 1.0f) * 0.5f);
     while (bj * (bj + 1) / 2 > blk) --bj;
@@ -1444,13 +1449,12 @@ vie_status build_knn_graph_gpu(const void *W_dev, int dtype, int64_t V, int d, i
         if (he == hipSuccess) he = hipMemsetAsync(b.count, 0, (size_t)V * 4, s);
         if (he == hipSuccess) {
             const int64_t nt = (V + kPairTileC - 1) / kPairTileC;
-            const int sb = nt >= 64 ? 8 : nt >= 16 ? 4 : 1;
-            const int64_t nsb = (nt + sb - 1) / sb;
-            const int64_t wgs = (nsb * (nsb + 1) / 2 + 7) / 8 * 8 * sb * sb * (kPairTileC / kPairTileJ);
+            const int64_t nsb = (nt + kPairBlock - 1) / kPairBlock;
+            const int64_t wgs = (nsb * (nsb + 1) / 2 + 7) / 8 * 8 * kPairBlock * kPairBlock * (kPairTileC / kPairTileJ);
             auto kern = dtype == VIE_BF16 ? knn_pairs_kernel<true> : knn_pairs_kernel<false>;
             he = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kPairLds);
             if (he == hipSuccess) {
-                kern<<<(unsigned)wgs, kPairThreads, kPairLds, s>>>(W, V, row_bytes, sb, b.thr, b.nleft + 1, b.count, keys);
+                kern<<<(unsigned)wgs, kPairThreads, kPairLds, s>>>(W, V, row_bytes, b.thr, b.nleft + 1, b.count, keys);
                 he = hipGetLastError();
             }
         }
