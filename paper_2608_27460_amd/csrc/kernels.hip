@@ -2130,7 +2130,8 @@ __global__ __launch_bounds__(NT) void hnsw_kernel(
 // HBM.
 //
 // A team (TeamArgs) runs this on several workgroups per query that divide
-// only the scoring and pass each other the kept keys every step; row sharing
+// the claims and the scoring of the new nodes and pass each other the kept
+// keys every step; row sharing
 // (ShareArgs) lets the queries of a group reuse each other's scores.  Both
 // leave every decision, and so the traversal, exactly as above.
 
@@ -3697,7 +3698,9 @@ TeamArgs team_layout(void *ws, int team, int slot)
 size_t hnsw_team_workspace_bytes(const HnswLaunch &a)
 {
     if (a.team <= 1) return 0;
-    // (the last part, three words a member, is spare: callers know this size)
+    // The last part, three words a member, held the counts that now travel in
+    // the lines.  It stays in the size, so that a workspace sized by a library
+    // with either layout serves both.
     return round256((size_t)a.B * 3 * a.team * team_slot(a) * 8) + round256((size_t)a.B * 3 * a.team * 8);
 }
 
