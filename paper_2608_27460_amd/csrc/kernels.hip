@@ -3432,9 +3432,15 @@ bool bf16_tiles(int64_t V, int row_bytes, int nq, int k)
     return large && tile_plan(V, true, k).rows_per_blk >= 112;
 }
 
-// The batch kernels: rows of 16-byte pieces, all 16-byte aligned.
-bool use_batch(int row_bytes, int B, const void *W, const void *h)
+// The batch kernels: rows of 16-byte pieces, all 16-byte aligned.  A few
+// queries (one pass, vnb, of the vector ALUs) over a few hundred fp32 rows
+// stay there, where more workgroups share them and nothing waits for the fp64
+// matrix steps of a whole row, a chain as long for few rows as for many (us
+// per call, vector / tiles: 100 x 4096, 3 queries 47 / 112; 512 x 1500, 8
+// queries 43 / 49; but 300 x 512 25 / 24, 800 x 1500 73 / 50).
+bool use_batch(int dtype, int64_t V, int row_bytes, int B, int vnb, const void *W, const void *h)
 {
+    if (dtype == VIE_F32 && B <= vnb && (V <= 256 || (V <= 512 && row_bytes >= 4000))) return false;
     return B >= kBatchMinB && row_bytes % 16 == 0 && (uintptr_t)W % 16 == 0 && (uintptr_t)h % 16 == 0;
 }
 
@@ -3535,7 +3541,7 @@ vie_status launch_dense_topk(const void *W, int dtype, int64_t V, int d, const v
     uint64_t *tops = reinterpret_cast<uint64_t *>(static_cast<char *>(ws) +
                                                    (((size_t)nbw * V * 4 + 255) & ~(size_t)255));
     const char *hb = static_cast<const char *>(h);
-    if (use_batch(row_bytes, B, W, h)) {
+    if (use_batch(dtype, V, row_bytes, B, p.nbmax, W, h)) {
         for (int q0 = 0; q0 < B; q0 += kBatchMaxNB) {
             const int nq = B - q0 < kBatchMaxNB ? B - q0 : kBatchMaxNB;
             const char *hp = hb + (int64_t)q0 * row_bytes;

@@ -133,6 +133,11 @@ def test_dense_topk_matches_oracle(vie, V, d, dtype, B, k):
     (66000, 24, synth.F32, 5, 1024),   # several slabs per workgroup
     (9001, 64, synth.BF16, 9, 900),    # most of the listed keys
     (300, 516, synth.F32, 3, 300),     # k = V: every listed key
+    # fp32, few rows: the vector ALUs up to 256 rows (512 long ones), tiles beyond
+    (256, 64, synth.F32, 8, 100),
+    (257, 64, synth.F32, 8, 100),
+    (512, 1000, synth.F32, 8, 300),
+    (513, 1000, synth.F32, 4, 300),
     # bf16, tiles with the blocks dealt to the workgroups in turn
     (139999, 24, synth.BF16, 3, 20),   # five blocks, the last one on some workgroups only
     (140003, 24, synth.BF16, 40, 600),  # three slabs of two blocks a workgroup, the last run short
@@ -192,6 +197,28 @@ def test_dense_batch_time_does_not_jump_with_k(vie, dtype):
         torch.cuda.synchronize()
         took[k] = min(took.get(k, 1.0), time.perf_counter() - t)
     assert took[300] < 4 * took[128], took
+
+
+def best_time(head, h, k, reps):
+    took = 1.0
+    for _ in range(3):
+        head(h, k)
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        for _ in range(reps):
+            head(h, k)
+        torch.cuda.synchronize()
+        took = min(took, (time.perf_counter() - t) / reps)
+    return took
+
+
+def test_a_small_fp32_batch_over_few_rows_does_not_wait_for_tiles(vie):
+    # nine queries take the matrix cores; three had taken as long
+    W = torch.randn(100, 4096, device="cuda")
+    h = torch.randn(9, 4096, device="cuda")
+    took = [best_time(vie.DenseHead(W, max_batch=9, max_k=50), h[:B], 50, 50) for B in (3, 9)]
+    say("100 x 4096 fp32: three queries %.1f us, nine %.1f us" % (took[0] * 1e6, took[1] * 1e6))
+    assert took[0] < 0.75 * took[1], took
 
 
 @pytest.mark.parametrize("V,d,most", [(65536, 4096, 1.25), (262144, 1000, 1.5)])
