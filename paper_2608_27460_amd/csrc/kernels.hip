@@ -3490,10 +3490,11 @@ hipError_t tile_launch_form(const void *W, int64_t V, int row_bytes, const char 
     // (fp32) or would fill more than half of it (bf16, in turn with other
     // memory: 128256 x 1024, 16 queries 56 us streamed, 61 through the cache), a
     // smaller one may still be there at the next call (50257 x 1000 bf16, 5
-    // queries: 28 us, 32 when streamed).  Lines that two stages share are not.
+    // queries: 28 us, 32 when streamed).  Not if two stages share a line: streamed,
+    // it is fetched for each (262144 x 1500 fp32, 3 queries: 311 us, 421; 128256 x
+    // 3000 bf16, 16 queries 149, 212).
     constexpr int kNt = 2;
-    const bool nt = BF16 ? row_bytes % 128 == 0 && V * row_bytes > (int64_t)128 << 20
-                         : V * row_bytes > (int64_t)256 << 20;
+    const bool nt = row_bytes % 128 == 0 && V * row_bytes > (int64_t)(BF16 ? 128 : 256) << 20;
     if constexpr (!BF16)
         if (p.row_tiles == 2)
             return nt ? tile_launch<BF16, NQT, 2, kNt>(W, V, row_bytes, h, nq, k, p, zbuf, tops, ids, logits, s)

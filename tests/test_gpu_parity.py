@@ -221,6 +221,18 @@ def test_a_small_fp32_batch_over_few_rows_does_not_wait_for_tiles(vie):
     assert took[0] < 0.75 * took[1], took
 
 
+def test_rows_that_share_lines_stream_like_rows_that_do_not(vie):
+    # fp32 rows of 6000 and 6016 bytes (47 lines): read past the caches, a line
+    # that two stages share was fetched for each
+    took = []
+    for d in (1500, 1504):
+        W = torch.empty(128256, d, device="cuda").normal_()
+        took.append(best_time(vie.DenseHead(W, max_batch=4, max_k=50), torch.randn(4, d, device="cuda"), 50, 10))
+        del W
+    say("128256 x 1500 fp32, four queries: %.1f us, x 1504 %.1f us" % (took[0] * 1e6, took[1] * 1e6))
+    assert took[0] < 1.19 * took[1], took
+
+
 @pytest.mark.parametrize("V,d,most", [(65536, 4096, 1.25), (262144, 1000, 1.5)])
 def test_a_small_bf16_batch_streams_like_one_query(vie, V, d, most):
     # one pass over W_out either way: half a GB, which bounds both.  (Tiles for
