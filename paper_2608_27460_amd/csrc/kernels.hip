@@ -2651,7 +2651,10 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
                     }
             }
         } else {
-            // N entries a thread, NT apart, from entry b0 on
+            // N entries a thread, NT apart, from entry b0 on.  A lane of one
+            // workgroup without an entry claims nothing (an OR of zero) in a
+            // word of its own, with no branch between the claims.
+            const int own = V >= 32 * kWave ? lane : 0;
             auto claim_some = [&](auto count, int b0) {
                 constexpr int N = decltype(count)::value;
                 int32_t ev[N];
@@ -2680,17 +2683,19 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
 #pragma unroll
                 for (int u = 0; u < N; ++u) {
                     old[u] = ~0u;
-                    if (ev[u] >= 0) old[u] = atomicOr(&vis[ev[u] >> 5], 1u << (ev[u] & 31));
+                    if constexpr (FORM == Form::kOne)
+                        old[u] = atomicOr(&vis[ev[u] >= 0 ? ev[u] >> 5 : own], ev[u] >= 0 ? 1u << (ev[u] & 31) : 0u);
+                    else if (ev[u] >= 0)
+                        old[u] = atomicOr(&vis[ev[u] >> 5], 1u << (ev[u] & 31));
                 }
 #pragma unroll
                 for (int u = 0; u < N; ++u)
-                    if (!(old[u] & (1u << (ev[u] & 31)))) cid[atomicAdd(&sh.nnew, 1u)] = ev[u];
+                    if (ev[u] >= 0 && !(old[u] & (1u << (ev[u] & 31)))) cid[atomicAdd(&sh.nnew, 1u)] = ev[u];
             };
-            // As many entries as the rest holds, and no claim without an entry:
-            // claims of nothing meet on one word of the bitmap and are served
-            // one by one.  One query on one workgroup, int8 rows: 95668 x 656
-            // at 8 per step, ef 685, 1423 -> 1277 us; 9488 x 704 (bf16 rows) at
-            // 32 per step, ef 372, 266 -> 236 us.
+            // As many entries as the rest holds: claims of nothing on one word
+            // of the bitmap are served one by one.  One query on one workgroup,
+            // int8 rows: 95668 x 656 at 8 per step, ef 685, 1423 -> 1277 us;
+            // 9488 x 704 (bf16 rows) at 32 per step, ef 372, 266 -> 236 us.
             int b0 = 0;
             for (; ncl - b0 > 2 * NT; b0 += kClaimBatch * NT) claim_some(std::integral_constant<int, kClaimBatch>(), b0);
             if (ncl - b0 > NT) claim_some(std::integral_constant<int, 2>(), b0);
@@ -2732,11 +2737,18 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
         for (int j = grp; j < nl; j += 2 * kGroups, r += 2) {
             const int32_t ea = lst[j];
             const int32_t eb = j + kGroups < nl ? lst[j + kGroups] : -1;
+            // One workgroup: the lane's place opaque in each round, so that
+            // which of its chunks and list entries exist is compared again.
+            // Held over the loop these masks took more scalar registers than
+            // there are, and two lane reads each before every load: 100000 x
+            // 512 bf16, lists of 128, 32 per step, ef 300, 338 us, now 322.
+            int gc = gl;
+            if constexpr (FORM == Form::kOne) asm("" : "+v"(gc));
             int32_t la[PF], lb[PF];
             if (cache_on && r < kMultiHeld) {
 #pragma unroll
                 for (int u = 0; u < PF; ++u) {
-                    const int t = gl + u * G;
+                    const int t = gc + u * G;
                     la[u] = t < M0 ? adj0[(int64_t)ea * M0 + t] : -1;
                     lb[u] = t < M0 && eb >= 0 ? adj0[(int64_t)eb * M0 + t] : -1;
                 }
@@ -2775,7 +2787,7 @@ __global__ __launch_bounds__(NT) void hnsw_multi_kernel(
                 sa = q8_score(ia, ca, hscale);
                 sb = q8_score(ib, cb, hscale);
             } else {
-                row_dot2<VEC, BF16, G>(W, ea, eb, row_bytes, hs, gl, sa, sb);
+                row_dot2<VEC, BF16, G>(W, ea, eb, row_bytes, hs, gc, sa, sb);
             }
             const uint64_t ka = make_key(sa, ea), kb = eb >= 0 ? make_key(sb, eb) : 0ull;
             if (gl == 0 && ka > worst) {
