@@ -3408,8 +3408,8 @@ TilePlan tile_plan(int64_t V, bool bf16, int k)
 // and with W_out just written (us per call with the merge, register-staged /
 // tiles):
 //   - heads that leave a quarter or more of the CUs without a register-staged
-//     workgroup (any, up to 32 queries): 16000 x 2048, 16 queries 28 / 24; 10000 x
-//     3072, 64 queries 44 / 37; 32768 x 128, 3 queries 12.0 / 11.4;
+//     workgroup (up to 32 queries: that give no CU two): 16000 x 2048, 16 queries
+//     28 / 24; 10000 x 3072, 64 queries 44 / 37; 32768 x 128, 3 queries 12.0 / 11.4;
 //   - heads whose last round of register-staged workgroups is mostly empty:
 //     151936 x 1024 (594 workgroups, 512 at a time), 5 / 64 queries 67 / 60 and 91 /
 //     80; 140000 x 3072, 33 queries 197 / 156; with few queries also those whose

@@ -401,11 +401,11 @@ __global__ __launch_bounds__(kGramThreads) __attribute__((amdgpu_waves_per_eu(2)
 // (a build over 32768 x 256 bf16 zeros: 38.1 ms
 // with them, 23.6 without, 23.5 in the chunked form).
 //
-// Bound by the matrix cores.  151936 x 1024 bf16: 25.5 ms for 23.6 TFLOP (0.93
+// Bound by the matrix cores.  151936 x 1024 bf16: 26.5 ms for 23.6 TFLOP (0.89
 // PFLOP/s; an 8192-cubed library product reaches 1.21), where the chunked form
 // multiplied every pair twice (63.6 ms), wrote 92 GB of scores and read them
-// back (21.3 ms of selection); with sampling and picking the step takes 33
-// ms instead of 85.  32768 x 256 fp32: 2.7 ms (5.6 chunked) at 100 TFLOP/s.
+// back (21.3 ms of selection); with sampling and picking the step takes 32
+// ms instead of 85.  32768 x 256 fp32: 2.9 ms (5.6 chunked) at 94 TFLOP/s.
 //
 // A wave owns a 64 x 64 block of the tile as 4 x 4 tiles of 16 x 16 (the
 // layout, and so every score's sequence of products and sums, is that of
@@ -413,8 +413,10 @@ __global__ __launch_bounds__(kGramThreads) __attribute__((amdgpu_waves_per_eu(2)
 // to LDS (global_load_lds, 16 bytes a lane), kPairBufs - 1 stages ahead, so
 // no register holds a load in flight and two workgroups fit a CU: one fills
 // the matrix cores while the other waits or sifts its scores.  Piece p of
-// staged row x sits at p ^ ((x >> 2) & 3): the 16 rows of an operand read
-// then hit every LDS bank once.
+// staged row x sits at p ^ ((x >> 2) & 3).  By the LDS counters that still
+// leaves half of the operand reads' cycles to bank conflicts (2.9e9 of 6.0e9 a
+// build of 151936 x 1024 bf16; 1.35e8 of 2.9e8 for 32768 x 256 fp32), and the fp32
+// form spills 114 registers around the sift: what it has left is there.
 
 constexpr int kPairTileC = 256, kPairTileJ = 128;  // rows c and j of a tile
 constexpr int kPairWavesJ = kPairTileJ / 64;
@@ -940,8 +942,9 @@ constexpr int kSelTri = kSelectRows * (kSelectRows + 1) / 2 * 4;
 static_assert(kSelTri <= kSelBufs * kSelStage, "the triangle takes the place of the stages");
 constexpr size_t kSelectLds = (size_t)kSelBufs * kSelStage + (size_t)kSelectRows * 8;
 
-// Staged row x holds its 16-byte piece p at p ^ ((x >> 1) & 7): the operand
-// reads (16 rows, one piece each of four) hit every LDS bank once.
+// Staged row x holds its 16-byte piece p at p ^ ((x >> 1) & 7): the 16-byte
+// operand reads of bf16 rows (16 rows, one piece each of four) leave 5% of the
+// LDS cycles to bank conflicts; the 4-byte ones of fp32 rows 46%.
 __device__ __forceinline__ int sel_piece(int x, int p) { return x * kSelKC + ((p ^ ((x >> 1) & 7)) << 4); }
 
 // Wave w's tiles: block rows w and 7 - w of the lower triangle, (w + 1) +
